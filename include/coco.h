@@ -53,7 +53,8 @@
  *   1 KB block (n / 16) * (K / 32) + k / 32 holds rows 16 (n / 16) .. + 15 and
  *   k 32 (k / 32) .. + 31 as 64 chunks of 8 consecutive k, chunk
  *   ((k % 32) / 8) * 16 + n % 16 -- one MFMA operand fragment per 16 rows x
- *   32 k, read by one contiguous 1 KB load.
+ *   32 k, read by one contiguous 1 KB load. The copy of w_gate_up interleaves
+ *   its rows: 8 gate rows, then the 8 matching up rows, in every block.
  * Paged cache of one layer, with block size B = 16 tokens:
  *   k_cache, v_cache [num_blocks][Hkv][B * hd]: one tile of B tokens x hd
  *   dimensions per (block, kv head), in MFMA operand order. Inside a tile,
@@ -243,8 +244,8 @@ enum {
   COCO_WS_O = 3,  /* attention output, [max_rows][Hq*hd], dtype */
   COCO_WS_X1 = 4, /* residual after the O projection, [max_rows][d], fp32 */
   COCO_WS_H2 = 5, /* RMSNorm_2 output, [max_rows][d], dtype (bf16 prefill
-                     with d a multiple of 256 folds the row's 1/rms into the
-                     gate/up projection and holds x1 * gamma_2 here) */
+                     folds the row's 1/rms into the gate/up projection and
+                     holds x1 * gamma_2 here) */
   COCO_WS_U = 6   /* SwiGLU activation, [max_rows][F], dtype */
 };
 int coco_layer_workspace(coco_layer_t h, int32_t which, void* dst, int64_t dst_bytes,

@@ -42,8 +42,9 @@ int fail(int code, const char* fmt, ...) {
 struct Work {
   void *x = nullptr, *h = nullptr, *q = nullptr, *o = nullptr, *h2 = nullptr, *u = nullptr;
   float *x1 = nullptr, *part = nullptr, *attn_o = nullptr, *attn_ml = nullptr;
-  // Row sums of squares: per K-slice (decode QKV with RMSNorm_1 folded in) or
-  // per 256-column tile (prefill O projection with RMSNorm_2 folded in).
+  // Row sums of squares per K-slice (decode QKV with RMSNorm_1 folded in). The
+  // prefill O projection's, per 32 columns ([rows][d / 32]), are in `part`,
+  // which prefill has no other use for.
   float* ss = nullptr;
   int32_t* split_off = nullptr;  // decode attention work list
   int32_t* row_info = nullptr;   // prefill row slots [rows][2] (position, cache block)
@@ -132,11 +133,21 @@ size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 int elem_bytes(int dtype) { return dtype == COCO_BF16 ? 2 : 4; }
 
-// Largest split count either GEMM path uses for (N, K).
-int gemm_splits(const coco_layer_config& c, int N, int K) {
+// Fp32 partials [splits][rows][N] that `part` has room for: the decode GEMMs'
+// K-slices, and at least one per 8192 k (up to four) where N < 12,288. The
+// prefill GEMMs write none; the floor keeps the size of a call's buffers, and
+// with it which calls the no-alloc entry point takes, what it was when
+// they split long K.
+int part_splits(const coco_layer_config& c, int N, int K) {
   if (c.dtype != COCO_BF16) return 1;
-  const int a = skinny_plan(N, K).S, b = tile_splits(N, K);
-  return a > b ? a : b;
+  int S = 1;
+  if ((N + 255) / 256 < 48) {
+    S = (K + 4096) / 8192;
+    S = S < 1 ? 1 : S > 4 ? 4 : S;
+    while (S > 1 && (K / 128) % S != 0) --S;
+  }
+  const int a = skinny_plan(N, K).S;
+  return a > S ? a : S;
 }
 
 // Lays out the per-call buffers for `rows` call rows and `dec_seqs` decode
@@ -151,7 +162,7 @@ size_t carve_work(const coco_layer_config& c, int64_t rows, int64_t dec_seqs, in
   int64_t part_elems = 0;
   const int64_t shapes[4][2] = {{nqkv, d}, {d, qd}, {2 * F, d}, {d, F}};
   for (auto& sh : shapes) {
-    const int64_t e = (int64_t)gemm_splits(c, (int)sh[0], (int)sh[1]) * R * sh[0];
+    const int64_t e = (int64_t)part_splits(c, (int)sh[0], (int)sh[1]) * R * sh[0];
     if (e > part_elems) part_elems = e;
   }
   const bool bf = c.dtype == COCO_BF16;
@@ -171,7 +182,6 @@ size_t carve_work(const coco_layer_config& c, int64_t rows, int64_t dec_seqs, in
       bf ? align256((size_t)dec_seqs * c.n_q_heads * max_splits * 2 * 4) : 0,    // attn_ml
       align256((size_t)(2 * dec_seqs + 2) * 4),  // split_off (decode attention work list)
       // ss: per-slice row sums of squares (decode QKV, at most 16 K-slices)
-      // or per-column-tile ones (prefill O projection, at most 32 tiles)
       align256((size_t)32 * R * 4),
       align256(R * 8)};  // row_info
   size_t off[13], total = 0;
@@ -306,8 +316,12 @@ int pack_weights(coco_layer* H) {
     coco_layer_weights& w = H->layers[l];
     const void** src[4] = {&w.w_qkv, &w.w_o, &w.w_gate_up, &w.w_down};
     for (int i = 0; i < 4; ++i) {
-      if (launch_pack_tile_order((const uint16_t*)*src[i], (int)mats[i].N, (int)mats[i].K,
-                                 (uint16_t*)p, nullptr) != hipSuccess) {
+      const hipError_t e =
+          i == 2 ? launch_pack_gate_up((const uint16_t*)*src[i], c.d_ffn, c.d_model,
+                                       (uint16_t*)p, nullptr)
+                 : launch_pack_tile_order((const uint16_t*)*src[i], (int)mats[i].N,
+                                          (int)mats[i].K, (uint16_t*)p, nullptr);
+      if (e != hipSuccess) {
         (void)hipGetLastError();
         (void)hipFree(H->packed);
         H->packed = nullptr;
@@ -581,20 +595,15 @@ int validate_batch(coco_layer* H, int64_t hidden_rows, const int32_t* row_idx, i
 // ----------------------------------------------------------------------------
 // Launch sequence.
 // ----------------------------------------------------------------------------
-// Decode uses the weight-streaming plan (split-K from (N, K) only); prefill
-// uses the large-tile kernel with one split.
+// The GEMMs that write fp32 partials (decode and fp32; bf16 prefill GEMMs
+// finish their consumer's work instead). bf16: the weight-streaming plan
+// (split-K from (N, K) only).
 template <typename T>
-int gemm(float* part, const T* A, const T* W, int M, int N, int K, bool prefill, int* S,
-         hipStream_t st);
+int gemm(float* part, const T* A, const T* W, int M, int N, int K, int* S, hipStream_t st);
 
 template <>
-int gemm<bf16_t>(float* part, const bf16_t* A, const bf16_t* W, int M, int N, int K,
-                 bool prefill, int* S, hipStream_t st) {
-  if (prefill) {
-    *S = tile_splits(N, K);
-    HIPCHK(launch_gemm_tile_bf16(A, W, part, M, N, K, *S, st));
-    return COCO_OK;
-  }
+int gemm<bf16_t>(float* part, const bf16_t* A, const bf16_t* W, int M, int N, int K, int* S,
+                 hipStream_t st) {
   const SkinnyPlan plan = skinny_plan(N, K);
   if (plan.waves == 0) return fail(COCO_EINVAL, "no GEMM plan for N=%d K=%d", N, K);
   *S = plan.S;
@@ -603,29 +612,43 @@ int gemm<bf16_t>(float* part, const bf16_t* A, const bf16_t* W, int M, int N, in
 }
 
 template <>
-int gemm<float>(float* part, const float* A, const float* W, int M, int N, int K, bool prefill,
-                int* S, hipStream_t st) {
-  (void)prefill;
+int gemm<float>(float* part, const float* A, const float* W, int M, int N, int K, int* S,
+                hipStream_t st) {
   *S = 1;
   HIPCHK(launch_gemm_f32(A, W, part, M, N, K, st));
   return COCO_OK;
 }
 
-// SwiGLU runs in the gate/up GEMM's epilogue whenever that GEMM is not split
-// along K (bf16; decode and prefill kernels each have a fused variant).
+// Decode: SwiGLU runs in the gate/up GEMM's epilogue whenever that GEMM is not
+// split along K (bf16).
 template <typename T>
-bool fused_swiglu(bool prefill, int F, int K) {
-  if (!std::is_same<T, bf16_t>::value) return false;
-  return prefill ? tile_splits(2 * F, K) == 1 : skinny_plan(2 * F, K).S == 1;
+bool fused_swiglu(int F, int K) {
+  return std::is_same<T, bf16_t>::value && skinny_plan(2 * F, K).S == 1;
+}
+
+// Decode: whether the (unsplit, bf16) gate/up projection of M rows runs on the
+// prefill tile kernel: above 128 rows, where the skinny kernel reads the
+// weights twice, and above 64 where a grid of 128 x 256 tiles fills at least
+// three quarters of the CUs. Measured, skinny kernel against tiles (us): 8B
+// 128 rows 56.2 / 55.9, 160 rows 74.4 / 65.0, 400 rows 154 / 89; 32B (216
+// tiles) 65 rows 121 / 106, 128 rows 135 / 116; 70B (224 tiles) 80 rows 186 /
+// 176, 128 rows 200 / 177, 256 rows 310 / 210. 8B (112 such tiles) 80 rows
+// 49.3 / 51.6, and at 64 rows 45.4 / 46.5 (70B 172 / 174): those stay.
+bool tile_swiglu(const coco_layer* H, int M) {
+  const int F = H->cfg.d_ffn;
+  return (M > 128 || (M > 64 && 2 * F / 256 >= H->num_cus * 3 / 4)) &&
+         skinny_plan(2 * F, H->cfg.d_model).S == 1;
 }
 
 // Layout of the four projections' A operands in a call: tile order
 // (tile_off) wherever the consuming GEMM reads it so -- every bf16 prefill
-// GEMM, and the decode GEMMs that run the row-split kernel -- else row-major.
+// GEMM, and the decode GEMMs that run the row-split or the tile kernel -- else
+// row-major.
 struct ActLayout {
   bool h = false, o = false, h2 = false, u = false;
 };
-ActLayout act_layout(const coco_layer_config& c, bool prefill, int M) {
+ActLayout act_layout(const coco_layer* H, bool prefill, int M) {
+  const coco_layer_config& c = H->cfg;
   ActLayout a;
   if (c.dtype != COCO_BF16) return a;
   if (prefill) {
@@ -634,7 +657,7 @@ ActLayout act_layout(const coco_layer_config& c, bool prefill, int M) {
   }
   const int d = c.d_model, F = c.d_ffn, qd = c.n_q_heads * c.head_dim;
   a.o = skinny_reads_tiled(d, qd, M, false);
-  a.h2 = skinny_reads_tiled(2 * F, d, M, skinny_plan(2 * F, d).S == 1);
+  a.h2 = tile_swiglu(H, M) || skinny_reads_tiled(2 * F, d, M, skinny_plan(2 * F, d).S == 1);
   a.u = skinny_reads_tiled(d, F, M, false);
   return a;
 }
@@ -683,6 +706,55 @@ int attention<float>(coco_layer* H, const Work& W, const coco_layer_weights& w, 
   return COCO_OK;
 }
 
+#define TIMED(kind, stmt)                     \
+  do {                                        \
+    KernelTimer timer_(H, kind, st);          \
+    stmt;                                     \
+  } while (0)
+
+// One bf16 prefill layer: x_src[x_idx] (null: in place) to y[y_idx]. Six
+// kernels; every GEMM runs its consumer's work in its epilogue: the QKV
+// projection RoPE and the cache append, the O projection the residual and
+// RMSNorm_2's first half (bf16(x1 * gamma) with sums of x1^2), gate/up the
+// 1/rms and the SwiGLU, down the residual and the scatter. rs: row slots for
+// the QKV epilogue, written by the first layer's gather.
+int prefill_layer(coco_layer* H, const Work& W, const coco_layer_weights& w, const bf16_t* x_src,
+                  const int32_t* x_idx, bf16_t* y, const int32_t* y_idx, int M,
+                  const int32_t* positions, const int32_t* seq_starts, int n_seqs,
+                  const int32_t* bt, const int32_t* ctx, const RowSlotArgs& rs, hipStream_t st) {
+  const coco_layer_config& c = H->cfg;
+  const int d = c.d_model, F = c.d_ffn, qd = c.n_q_heads * c.head_dim;
+  bf16_t *h = (bf16_t*)W.h, *o = (bf16_t*)W.o, *h2 = (bf16_t*)W.h2, *u = (bf16_t*)W.u;
+  TIMED(COCO_K_GATHER_NORM,
+        HIPCHK(launch_gather_rmsnorm<bf16_t>(x_src, x_idx, M, d, (const bf16_t*)w.gamma_attn,
+                                             c.rms_eps, nullptr, h, true, rs, st)));
+  PrefillEpiArgs qa;
+  qa.row_info = W.row_info;
+  qa.rope = H->rope;
+  qa.q_out = (uint16_t*)W.q;
+  qa.k_cache = (uint16_t*)w.k_cache;
+  qa.v_cache = (uint16_t*)w.v_cache;
+  qa.Hq = c.n_q_heads;
+  qa.Hkv = c.n_kv_heads;
+  TIMED(COCO_K_GEMM_QKV,
+        HIPCHK(launch_prefill_qkv_bf16(h, (const bf16_t*)w.w_qkv, M, d, qa, H->num_cus, st)));
+  int rc;
+  if ((rc = attention<bf16_t>(H, W, w, M, positions, seq_starts, n_seqs, bt, ctx, true, st)))
+    return rc;
+  float* const ss = W.part;
+  TIMED(COCO_K_GEMM_O,
+        HIPCHK(launch_prefill_resid_bf16(o, (const bf16_t*)w.w_o, M, d, qd, x_src, x_idx,
+                                         (const bf16_t*)w.gamma_mlp, W.x1, h2, ss, H->num_cus,
+                                         st)));
+  TIMED(COCO_K_GEMM_GATE_UP,
+        HIPCHK(launch_prefill_swiglu_bf16(h2, (const bf16_t*)w.w_gate_up, u, M, F, d, ss,
+                                          c.rms_eps, H->num_cus, st)));
+  TIMED(COCO_K_GEMM_DOWN,
+        HIPCHK(launch_prefill_scatter_bf16(u, (const bf16_t*)w.w_down, M, d, F, W.x1, y, y_idx,
+                                           H->num_cus, st)));
+  return COCO_OK;
+}
+
 template <typename T>
 int run_span(coco_layer* H, const Work& W, int first, int nl, T* hidden, const int32_t* row_idx,
              int M, const int32_t* positions, const int32_t* seq_starts, int n_seqs,
@@ -690,6 +762,7 @@ int run_span(coco_layer* H, const Work& W, int first, int nl, T* hidden, const i
   const coco_layer_config& c = H->cfg;
   const int d = c.d_model, Hq = c.n_q_heads, Hkv = c.n_kv_heads, hd = c.head_dim, F = c.d_ffn;
   const int nqkv = (Hq + 2 * Hkv) * hd;
+  constexpr bool kBf16 = std::is_same<T, bf16_t>::value;
   T* x = (T*)W.x;
   T* h = (T*)W.h;
   T* q = (T*)W.q;
@@ -698,61 +771,39 @@ int run_span(coco_layer* H, const Work& W, int first, int nl, T* hidden, const i
   T* u = (T*)W.u;
   int S, rc;
   const bool pre = seq_starts != nullptr;
-  const ActLayout lay = act_layout(c, pre, M);
-#define TIMED(kind, stmt)                     \
-  do {                                        \
-    KernelTimer timer_(H, kind, st);          \
-    stmt;                                     \
-  } while (0)
+  const ActLayout lay = act_layout(H, pre, M);
   for (int l = first; l < first + nl; ++l) {
     const coco_layer_weights& w = H->layers[l];
     const bool first_l = l == first, last_l = l == first + nl - 1;
-    // Decode (bf16) folds the gather and RMSNorm_1 into the QKV projection:
-    // it stages bf16(x * gamma) straight from the input rows and the QKV
-    // epilogue applies each row's 1/rms. Otherwise a gather + RMSNorm_1
-    // kernel writes h first. The residual reads the input rows where they
-    // are (hidden[row_idx] in the first layer of the call), so no copy of
-    // them is made.
-    const bool fold_norm = !pre && std::is_same<T, bf16_t>::value;
-    // Prefill QKV projection with RoPE and the cache append in its epilogue:
-    // the narrow-tile GEMM (whole rotation pairs per tile) when the head
-    // count has a plan, else the 256 x 256 tile GEMM.
-    const bool narrow_qkv =
-        pre && std::is_same<T, bf16_t>::value && hd == 128 && narrow_qkv_tile_n(Hq, Hkv, d) != 0;
-    const bool fuse_qkv =
-        narrow_qkv || (pre && std::is_same<T, bf16_t>::value && tile_qkv_fusable(Hq, Hkv, d));
-    // Prefill O and down projections on the narrow-tile GEMM (256 x d/32
-    // tiles, unsplit), when d has such a plan and the SwiGLU runs in the
-    // gate/up epilogue: the O epilogue then folds in the residual and
-    // RMSNorm_2's first half, the down epilogue the residual and the scatter.
-    const int ntn = pre && std::is_same<T, bf16_t>::value ? narrow_tile_n(d) : 0;
-    const bool narrow_o = ntn != 0 && (Hq * hd) % 128 == 0 && fused_swiglu<T>(pre, F, d);
-    const bool narrow_down = ntn != 0 && F % 128 == 0;
-    const bool fold_norm2 =
-        narrow_o ||
-        (pre && std::is_same<T, bf16_t>::value && tile_norm2_foldable(d, Hq * hd, F));
-    const int norm_tiles = narrow_o ? d / ntn : d / 256;
-    const T* x_src = first_l ? hidden : x;                     // this layer's input rows
+    // The residual reads the input rows where they are (hidden[row_idx] in
+    // the first layer of the call), so no copy of them is made; the last
+    // layer scatters to the full batch.
+    const T* x_src = first_l ? hidden : x;
     const int32_t* x_idx = first_l ? row_idx : nullptr;
-    // The fused prefill QKV epilogue reads each row's (position, cache block),
-    // written once per call by the first layer's gather.
+    T* const y = last_l ? hidden : x;
+    const int32_t* y_idx = last_l ? row_idx : nullptr;
+    // Prefill row slots (position, cache block), written once per call by the
+    // first layer's gather.
     RowSlotArgs rs;
-    if (fuse_qkv && first_l) {
-      rs.positions = positions;
-      rs.seq_starts = seq_starts;
-      rs.block_table = bt;
-      rs.row_info = W.row_info;
-      rs.n_seqs = n_seqs;
-      rs.max_blocks = c.max_blocks_per_seq;
-      rs.rope_rows = H->rope_rows;
-    }
-    if (!fold_norm)
-      TIMED(COCO_K_GATHER_NORM,
-            HIPCHK(launch_gather_rmsnorm<T>(first_l ? hidden : x, first_l ? row_idx : nullptr, M,
-                                            d, (const T*)w.gamma_attn, c.rms_eps,
-                                            nullptr, h, lay.h, rs, st)));
-    // QKV projection, RoPE, local cache append.
-    if (fold_norm) {
+    if constexpr (kBf16) {
+      if (pre) {
+        if (first_l) {
+          rs.positions = positions;
+          rs.seq_starts = seq_starts;
+          rs.block_table = bt;
+          rs.row_info = W.row_info;
+          rs.n_seqs = n_seqs;
+          rs.max_blocks = c.max_blocks_per_seq;
+          rs.rope_rows = H->rope_rows;
+        }
+        if ((rc = prefill_layer(H, W, w, x_src, x_idx, y, y_idx, M, positions, seq_starts,
+                                n_seqs, bt, ctx, rs, st)))
+          return rc;
+        continue;
+      }
+      // Decode folds the gather and RMSNorm_1 into the QKV projection: it
+      // stages bf16(x * gamma) straight from the input rows and the QKV
+      // epilogue applies each row's 1/rms.
       const SkinnyPlan plan = skinny_plan(nqkv, d);
       if (plan.waves == 0) return fail(COCO_EINVAL, "no GEMM plan for N=%d K=%d", nqkv, d);
       S = plan.S;
@@ -761,94 +812,37 @@ int run_span(coco_layer* H, const Work& W, int first, int nl, T* hidden, const i
                                                 (const bf16_t*)w.gamma_attn,
                                                 (const bf16_t*)w.w_qkv, W.part, W.ss, M, nqkv, d,
                                                 plan, st)));
-    } else if (narrow_qkv) {
-      NarrowEpiArgs qa;
-      qa.row_info = W.row_info;
-      qa.rope = H->rope;
-      qa.q_out = (uint16_t*)q;
-      qa.k_cache = (uint16_t*)w.k_cache;
-      qa.v_cache = (uint16_t*)w.v_cache;
-      qa.Hq = Hq;
-      qa.Hkv = Hkv;
-      TIMED(COCO_K_GEMM_QKV,
-            HIPCHK(launch_gemm_narrow_qkv_bf16((const uint16_t*)h, (const uint16_t*)w.w_qkv, M,
-                                               d, qa, st)));
-    } else if (fuse_qkv) {
-      // Prefill (bf16, QKV projection not split along K): RoPE and the cache
-      // append run in the GEMM's epilogue.
-      TileEpiArgs qa;
-      qa.row_info = W.row_info;
-      qa.rope = H->rope;
-      qa.q_out = (uint16_t*)q;
-      qa.k_cache = (uint16_t*)w.k_cache;
-      qa.v_cache = (uint16_t*)w.v_cache;
-      qa.Hq = Hq;
-      qa.Hkv = Hkv;
-      TIMED(COCO_K_GEMM_QKV,
-            HIPCHK(launch_gemm_tile_qkv_bf16((const uint16_t*)h, (const uint16_t*)w.w_qkv, M, d,
-                                             qa, st)));
     } else {
-      TIMED(COCO_K_GEMM_QKV, if ((rc = gemm<T>(W.part, h, (const T*)w.w_qkv, M, nqkv, d, pre, &S, st))) return rc);
+      // fp32: a gather + RMSNorm_1 kernel writes h first.
+      TIMED(COCO_K_GATHER_NORM,
+            HIPCHK(launch_gather_rmsnorm<T>(x_src, x_idx, M, d, (const T*)w.gamma_attn,
+                                            c.rms_eps, nullptr, h, false, rs, st)));
+      TIMED(COCO_K_GEMM_QKV,
+            if ((rc = gemm<T>(W.part, h, (const T*)w.w_qkv, M, nqkv, d, &S, st))) return rc);
     }
-    if (!fuse_qkv)
-      TIMED(COCO_K_QKV_EPILOGUE,
-            HIPCHK(launch_qkv_epilogue<T>(W.part, S, M, Hq, Hkv, hd, positions, seq_starts,
-                                          n_seqs, bt, c.max_blocks_per_seq, H->inv_freq, q,
-                                          (T*)w.k_cache, (T*)w.v_cache, ctx,
-                                          (seq_starts == nullptr && c.dtype == COCO_BF16)
-                                              ? W.split_off
-                                              : nullptr,
-                                          H->max_splits, fold_norm ? W.ss : nullptr, d,
-                                          c.rms_eps, st)));
+    // RoPE, local cache append.
+    TIMED(COCO_K_QKV_EPILOGUE,
+          HIPCHK(launch_qkv_epilogue<T>(W.part, S, M, Hq, Hkv, hd, positions, seq_starts, n_seqs,
+                                        bt, c.max_blocks_per_seq, H->inv_freq, q, (T*)w.k_cache,
+                                        (T*)w.v_cache, ctx, kBf16 ? W.split_off : nullptr,
+                                        H->max_splits, kBf16 ? W.ss : nullptr, d, c.rms_eps,
+                                        st)));
     // Attention over the paged cache.
     if ((rc = attention<T>(H, W, w, M, positions, seq_starts, n_seqs, bt, ctx, lay.o, st)))
       return rc;
-    // O projection + residual + RMSNorm_2. Prefill (bf16, unsplit O and
-    // gate/up projections): the O projection's epilogue adds the residual and
-    // writes bf16(x1 * gamma_2) with per-tile sums of x1^2; the gate/up
-    // epilogue applies each row's 1/rms, so no separate norm kernel runs.
-    if (narrow_o) {
-      TIMED(COCO_K_GEMM_O,
-            HIPCHK(launch_gemm_narrow_resid_bf16((const uint16_t*)o, (const uint16_t*)w.w_o, M,
-                                                 d, Hq * hd, (const uint16_t*)x_src, x_idx,
-                                                 (const uint16_t*)w.gamma_mlp, W.x1,
-                                                 (uint16_t*)h2, W.ss, st)));
-    } else if (fold_norm2) {
-      TIMED(COCO_K_GEMM_O,
-            HIPCHK(launch_gemm_tile_resid_bf16((const uint16_t*)o, (const uint16_t*)w.w_o, M, d,
-                                               Hq * hd, (const uint16_t*)x_src, x_idx,
-                                               (const uint16_t*)w.gamma_mlp, W.x1,
-                                               (uint16_t*)h2, W.ss, st)));
-    } else {
-      TIMED(COCO_K_GEMM_O, if ((rc = gemm<T>(W.part, o, (const T*)w.w_o, M, d, Hq * hd, pre, &S, st))) return rc);
-      TIMED(COCO_K_RESIDUAL_NORM,
-            HIPCHK(launch_residual_rmsnorm<T>(W.part, S, M, d, x_src, x_idx,
-                                              (const T*)w.gamma_mlp, c.rms_eps, W.x1, h2, lay.h2,
-                                              st)));
-    }
-    // SwiGLU MLP (prefill: SwiGLU in the gate/up GEMM's epilogue when the
-    // GEMM is not split along K).
-    if (fused_swiglu<T>(pre, F, d)) {
-      if (pre && fold_norm2 && narrow_swiglu_fits(F, d)) {
+    // O projection + residual + RMSNorm_2.
+    TIMED(COCO_K_GEMM_O,
+          if ((rc = gemm<T>(W.part, o, (const T*)w.w_o, M, d, Hq * hd, &S, st))) return rc);
+    TIMED(COCO_K_RESIDUAL_NORM,
+          HIPCHK(launch_residual_rmsnorm<T>(W.part, S, M, d, x_src, x_idx, (const T*)w.gamma_mlp,
+                                            c.rms_eps, W.x1, h2, lay.h2, st)));
+    // SwiGLU MLP.
+    if (fused_swiglu<T>(F, d)) {
+      if (tile_swiglu(H, M)) {
         TIMED(COCO_K_GEMM_GATE_UP,
-              HIPCHK(launch_gemm_narrow_swiglu_bf16((const uint16_t*)h2,
-                                                    (const uint16_t*)w.w_gate_up, (uint16_t*)u,
-                                                    M, F, d, W.ss, norm_tiles, c.rms_eps, st)));
-      } else if (pre) {
-        TIMED(COCO_K_GEMM_GATE_UP,
-              HIPCHK(launch_gemm_tile_swiglu_bf16((const bf16_t*)h2, (const bf16_t*)w.w_gate_up,
-                                                  (bf16_t*)u, M, F, d,
-                                                  fold_norm2 ? W.ss : nullptr, norm_tiles,
-                                                  c.rms_eps, st)));
-      } else if (c.dtype == COCO_BF16 && M > 128 && lay.h2 && lay.u &&
-                 narrow_swiglu_plain_fits(M, F, d)) {
-        // 129-256 rows with one round of 256 x 128 tiles (the 8B shape): the
-        // prefill tile kernel, bit-identical to the decode GEMM, in ~half its
-        // time (the row-split decode kernel streams 2.8 TB/s there).
-        TIMED(COCO_K_GEMM_GATE_UP,
-              HIPCHK(launch_gemm_narrow_swiglu_plain_bf16((const uint16_t*)h2,
-                                                          (const uint16_t*)w.w_gate_up,
-                                                          (uint16_t*)u, M, F, d, st)));
+              HIPCHK(launch_prefill_swiglu_plain_bf16((const uint16_t*)h2,
+                                                      (const uint16_t*)w.w_gate_up, (uint16_t*)u,
+                                                      M, F, d, lay.u, H->num_cus, st)));
       } else {
         TIMED(COCO_K_GEMM_GATE_UP,
               HIPCHK(launch_gemm_skinny_swiglu_bf16((const bf16_t*)h2,
@@ -857,27 +851,18 @@ int run_span(coco_layer* H, const Work& W, int first, int nl, T* hidden, const i
       }
     } else {
       TIMED(COCO_K_GEMM_GATE_UP,
-            if ((rc = gemm<T>(W.part, h2, (const T*)w.w_gate_up, M, 2 * F, d, pre, &S, st))) return rc);
+            if ((rc = gemm<T>(W.part, h2, (const T*)w.w_gate_up, M, 2 * F, d, &S, st))) return rc);
       TIMED(COCO_K_SWIGLU, HIPCHK(launch_swiglu<T>(W.part, S, M, F, u, lay.u, st)));
     }
-    // Down projection and residual; the last layer of the segment scatters to
-    // the full batch.
-    if (narrow_down) {
-      TIMED(COCO_K_GEMM_DOWN,
-            HIPCHK(launch_gemm_narrow_scatter_bf16((const uint16_t*)u, (const uint16_t*)w.w_down,
-                                                   M, d, F, W.x1,
-                                                   (uint16_t*)(last_l ? hidden : x),
-                                                   last_l ? row_idx : nullptr, st)));
-    } else {
-      TIMED(COCO_K_GEMM_DOWN, if ((rc = gemm<T>(W.part, u, (const T*)w.w_down, M, d, F, pre, &S, st))) return rc);
-      TIMED(COCO_K_RESIDUAL_SCATTER,
-            HIPCHK(launch_residual_scatter<T>(W.part, S, M, d, W.x1, last_l ? hidden : x,
-                                              last_l ? row_idx : nullptr, st)));
-    }
+    // Down projection and residual.
+    TIMED(COCO_K_GEMM_DOWN,
+          if ((rc = gemm<T>(W.part, u, (const T*)w.w_down, M, d, F, &S, st))) return rc);
+    TIMED(COCO_K_RESIDUAL_SCATTER,
+          HIPCHK(launch_residual_scatter<T>(W.part, S, M, d, W.x1, y, y_idx, st)));
   }
-#undef TIMED
   return COCO_OK;
 }
+#undef TIMED
 
 int check_batch(coco_layer* H, int first, int nl, const void* hidden, int64_t hidden_rows,
                 const int32_t* row_idx, int n_rows, const int32_t* positions,
@@ -945,7 +930,7 @@ int forward_impl(coco_layer* H, int first, int nl, void* hidden, int64_t hidden_
     return rc;
   }
   if (!use_static) {
-    const ActLayout a = act_layout(H->cfg, seq_starts != nullptr, n_rows);
+    const ActLayout a = act_layout(H, seq_starts != nullptr, n_rows);
     for (bool& t : H->ws_tiled) t = false;
     H->ws_tiled[COCO_WS_H] = a.h;
     H->ws_tiled[COCO_WS_O] = a.o;

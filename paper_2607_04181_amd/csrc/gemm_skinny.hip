@@ -19,9 +19,9 @@
 //     16-rows-per-instruction fragment reads hit distinct banks;
 //   * each 16x16 output tile is accumulated with v_mfma_f32_16x16x32_bf16 in
 //     ascending k.
-// A pass covers up to 128 rows. For batches of more than 128 rows (8-wave
-// and fused 7-wave plans) and of 65-128 rows (8-wave plans), a row-split
-// variant takes over (gemm_skinny_rows_kernel below): there the weight tile
+// A pass covers up to 128 rows. For batches of more than 64 rows and 8-wave
+// plans a row-split variant takes over (gemm_skinny_rows_kernel below; large
+// SwiGLU batches run the tile kernel of gemm_prefill.h): there the weight tile
 // of a stage goes to LDS and the row tiles are dealt to the waves, since every
 // wave reading the whole activation tile from LDS costs more LDS time as the
 // batch grows.
@@ -91,10 +91,11 @@ __device__ __forceinline__ u32x4_t scale_bf16x8(u32x4_t x, u32x4_t g) {
   return y;
 }
 
-// FUSE: W is the [2F][K] gate/up matrix (N = 2F, one K-slice). Lanes
-// c16 < 8 of a wave stream gate rows o0..o0+7 and lanes c16 >= 8 the
-// matching up rows, so the epilogue pairs lanes c16 and c16+8 and writes
-// h = silu(gate) * up in bf16 to H[M][F] instead of fp32 partials.
+// FUSE: W is the [2F][K] gate/up matrix (N = 2F, one K-slice), interleaved
+// (launch_pack_gate_up): lanes c16 < 8 of a wave stream gate rows o0..o0+7 and
+// lanes c16 >= 8 the matching up rows, so the epilogue pairs lanes c16 and
+// c16+8 and writes h = silu(gate) * up in bf16 to H[M][F] instead of fp32
+// partials.
 // NORM: A holds the layer input rows, row m of the call at A[row_idx[m]]
 // (row_idx null: row m); the staged operand is bf16(A * gamma) and
 // ss[blockIdx.y][m] receives the row's sum of squares over the K-slice
@@ -114,8 +115,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(
   const int lane = tid & 63, wv = tid >> 6;
   const int c16 = lane & 15, j4 = lane >> 4;
   const int o0 = (blockIdx.x * WAVES + wv) * 8;  // fused: this wave's 8 outputs
-  const int n_col = FUSE ? (c16 < 8 ? o0 + c16 : N / 2 + o0 + c16 - 8)
-                         : blockIdx.x * (16 * WAVES) + wv * 16 + c16;  // this lane's weight row
+  const int n_col = blockIdx.x * (16 * WAVES) + wv * 16 + c16;  // this lane's weight row
   const int k_begin = blockIdx.y * k_slice;
   const int stages = k_slice / kBK;
   float* out = FUSE ? nullptr : part + (int64_t)blockIdx.y * M * N;
@@ -244,10 +244,8 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_kernel(
 //     (global_load_lds, 16 bytes per lane; wave w fills the 16 rows of column
 //     tile w as two 1 KB loads, one per 32 k) into a ring of four slots, three
 //     stages in flight. LDS holds each 16 rows x 32 k in tile order (chunk
-//     (k / 8) * 16 + row), so a load reads one tile-order block of W (or, in
-//     the SwiGLU variant, the halves of two blocks that hold the tile's eight
-//     gate and eight up rows) and a fragment read gives each 16-lane group
-//     256 contiguous bytes;
+//     (k / 8) * 16 + row), so a load reads one tile-order block of W and a
+//     fragment read gives each 16-lane group 256 contiguous bytes;
 //   * row tile t of the pass (rows 16t .. 16t + 15) belongs to wave t % WAVES;
 //     a wave loads its tiles' activation fragments from memory straight into
 //     registers (A in tile order: one 1 KB block per load), AST stages deep (stage st + AST once stage st has been
@@ -295,20 +293,10 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_rows_kernel(
   const int stages = k_slice / kRK;
   float* out = FUSE ? nullptr : part + (int64_t)blockIdx.y * M * N;
 
-  // Weight row of workgroup row rho = 16 j + c (column tile j, column c of
-  // it): the rows wave j of gemm_skinny_kernel streams.
-  auto w_row = [&](int rho) -> int {
-    const int j = rho >> 4, c = rho & 15;
-    if (FUSE) {
-      const int o = (blockIdx.x * WAVES + j) * 8;
-      return c < 8 ? o + c : N / 2 + o + c - 8;
-    }
-    return blockIdx.x * NR + rho;
-  };
   // Direct load q of this wave: k 32q .. 32q + 31 of the stage for the 16
   // rows of column tile wv; lane l = 16 j4 + c16 lands at LDS chunk l of the
-  // slot's block 2 wv + q and reads row w_row(16 wv + c16), k 32q + 8 j4 ..
-  // + 7, which is chunk j4 * 16 + row % 16 of tile-order block
+  // slot's block 2 wv + q and reads the row that lane c16 of wave wv of
+  // gemm_skinny_kernel streams, k 32q + 8 j4 .. + 7, which is chunk j4 * 16 + row % 16 of tile-order block
   // (row / 16) * (K / 32) + k / 32.
   // Addresses are a uniform base (advanced per stage) plus a fixed 32-bit byte
   // offset per lane, so no address register is rewritten inside the loop (a
@@ -316,7 +304,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_skinny_rows_kernel(
   const char* wbase = (const char*)(W + (int64_t)(k_begin / 32) * 512);
   uint32_t woff[kDLoads];
   {
-    const int row = w_row(16 * wv + c16);
+    const int row = blockIdx.x * NR + 16 * wv + c16;
 #pragma unroll
     for (int q = 0; q < kDLoads; ++q)
       woff[q] = (uint32_t)((row >> 4) * (K / 32) + q) * 1024u +
@@ -485,20 +473,17 @@ hipError_t launch_plan(const uint16_t* A, const uint16_t* W, float* part, uint16
 }
 
 // Which kernel a plan of `waves` waves runs for M rows: the row-split kernel
-// where it measured faster, above 128 rows for 7- and 8-wave plans (8B
-// gate/up and down at 256 rows: 113 -> 89 us and 64 -> 46 us against two
-// 128-row passes; with fewer waves or the folded norm it measured slower),
-// and for 128-row passes of 8-wave plans. (No decode shape here has an
-// unfused 7-wave plan; those keep the 128-row kernel.) Its per-lane byte
-// offsets are 32-bit: both operands must be under 4 GB.
+// where it measured faster, for 8-wave plans above 64 rows (8B down at 256
+// rows: 64 -> 46 us against two 128-row passes; with fewer waves or the
+// folded norm it measured slower). The SwiGLU variant is called up to 128
+// rows. Its per-lane byte offsets are 32-bit: both operands must be under 4 GB.
 enum RowsKind { kNoRows = 0, kRows16, kRows8 };
 RowsKind rows_kind(int waves, bool fuse, bool norm, int N, int K, int M) {
-  if (M <= 64 || norm || !(waves == 8 || (waves == 7 && fuse))) return kNoRows;
+  if (M <= 64 || norm || waves != 8 || (fuse && M > 128)) return kNoRows;
   const bool fits = (int64_t)N * K * 2 < (int64_t(1) << 32) &&
                     (int64_t)((M + 15) / 16 * 16) * K * 2 < (int64_t(1) << 32);
   if (!fits) return kNoRows;
-  if (M > 128) return kRows16;
-  return waves == 8 ? kRows8 : kNoRows;
+  return M > 128 ? kRows16 : kRows8;
 }
 
 template <int WAVES, bool FUSE, bool NORM>
@@ -506,13 +491,15 @@ hipError_t launch_waves(const uint16_t* A, const uint16_t* W, float* part, uint1
                         int N, int K, int S, NormArgs na, bool h_tiled, hipStream_t st) {
   if (M <= 64)
     return launch_plan<WAVES, 4, FUSE, NORM>(A, W, part, H, M, N, K, S, na, h_tiled, st);
-  if constexpr ((WAVES == 8 || (WAVES == 7 && FUSE)) && !NORM) {
+  if constexpr (WAVES == 8 && !NORM) {
     switch (rows_kind(WAVES, FUSE, NORM, N, K, M)) {
       case kRows16:
-        COCO_LAUNCH((gemm_skinny_rows_kernel<WAVES, FUSE, 16, WAVES == 8 ? 4 : 2>),
-                    dim3(N / (16 * WAVES), S), dim3(WAVES * 64), 0, st, A, W, part, H, M, N,
-                    K, K / S, h_tiled);
-        return hipGetLastError();
+        if constexpr (!FUSE) {
+          COCO_LAUNCH((gemm_skinny_rows_kernel<8, false, 16, 4>), dim3(N / 128, S), dim3(512), 0,
+                      st, A, W, part, H, M, N, K, K / S, h_tiled);
+          return hipGetLastError();
+        }
+        break;
       case kRows8:
         COCO_LAUNCH((gemm_skinny_rows_kernel<8, FUSE, 8, 4>), dim3(N / 128, S), dim3(512), 0,
                     st, A, W, part, H, M, N, K, K / S, h_tiled);
@@ -632,24 +619,39 @@ hipError_t launch_gemm_skinny_swiglu_bf16(const uint16_t* A, const uint16_t* W_g
 // 16-byte chunk, read in row order.
 // ----------------------------------------------------------------------------
 namespace {
+// F > 0: rows interleaved as launch_pack_gate_up says (N = 2F).
 __global__ __launch_bounds__(256) void pack_tile_order_kernel(const u32x4_t* __restrict__ w,
-                                                              int64_t n_chunks, int K,
+                                                              int64_t n_chunks, int K, int F,
                                                               u32x4_t* __restrict__ out) {
   const int64_t chunk = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (chunk >= n_chunks) return;
   const int64_t per_row = K / 8;
-  const int64_t n = chunk / per_row, kc = chunk - n * per_row;
+  int64_t n = chunk / per_row;
+  const int64_t kc = chunk - n * per_row;
+  if (F > 0) {
+    const int64_t o = n < F ? n : n - F;
+    n = (o >> 3) * 16 + (n < F ? 0 : 8) + (o & 7);
+  }
   out[((n >> 4) * (K / 32) + (kc >> 2)) * 64 + (kc & 3) * 16 + (n & 15)] = w[chunk];
+}
+
+hipError_t pack(const uint16_t* W, int64_t N, int K, int F, uint16_t* out, hipStream_t st) {
+  const int64_t n_chunks = N * K / 8;
+  COCO_LAUNCH(pack_tile_order_kernel, dim3((unsigned)((n_chunks + 255) / 256)), dim3(256), 0, st,
+              (const u32x4_t*)W, n_chunks, K, F, (u32x4_t*)out);
+  return hipGetLastError();
 }
 }  // namespace
 
 hipError_t launch_pack_tile_order(const uint16_t* W, int N, int K, uint16_t* out,
                                   hipStream_t st) {
   if (N <= 0 || K <= 0 || N % 16 != 0 || K % 32 != 0) return hipErrorInvalidValue;
-  const int64_t n_chunks = (int64_t)N * K / 8;
-  COCO_LAUNCH(pack_tile_order_kernel, dim3((unsigned)((n_chunks + 255) / 256)), dim3(256), 0, st,
-              (const u32x4_t*)W, n_chunks, K, (u32x4_t*)out);
-  return hipGetLastError();
+  return pack(W, N, K, 0, out, st);
+}
+
+hipError_t launch_pack_gate_up(const uint16_t* W, int F, int K, uint16_t* out, hipStream_t st) {
+  if (F <= 0 || K <= 0 || F % 8 != 0 || K % 32 != 0) return hipErrorInvalidValue;
+  return pack(W, 2LL * F, K, F, out, st);
 }
 
 // ----------------------------------------------------------------------------

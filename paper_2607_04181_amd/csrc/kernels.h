@@ -73,8 +73,8 @@ hipError_t launch_residual_rmsnorm(const float* part, int S, int M, int d, const
                                    const int32_t* row_idx, const T* gamma, float eps, float* x1,
                                    T* h2, bool tiled, hipStream_t st);
 
-// u = silu(sum_s gate) * sum_s up, part rows [2F] = gate then up. tiled: u in
-// tile order.
+// u = silu(sum_s gate) * sum_s up, part rows [2F] = gate then up (fp32) or in
+// the interleaved order of launch_pack_gate_up (bf16). tiled: u in tile order.
 template <typename T>
 hipError_t launch_swiglu(const float* part, int S, int M, int F, T* u, bool tiled,
                          hipStream_t st);
@@ -103,6 +103,11 @@ hipError_t launch_kv_append(const T* k, const T* v, const int32_t* seq_idx,
 // 0, K % 32 == 0).
 hipError_t launch_pack_tile_order(const uint16_t* W, int N, int K, uint16_t* out,
                                   hipStream_t st);
+// The gate/up matrix [W_g; W_u] ([2F][K], F % 8 == 0) in tile order with its
+// rows interleaved: packed rows 16b .. 16b + 7 are gate rows 8b .. 8b + 7,
+// packed rows 16b + 8 .. 16b + 15 the matching up rows, so both factors of an
+// output come out of one 16-column MFMA tile.
+hipError_t launch_pack_gate_up(const uint16_t* W, int F, int K, uint16_t* out, hipStream_t st);
 
 // part[s][m][n] = sum_{k in slice s} A[m][k] * W[n][k]   (bf16 in, fp32 out)
 // The plan (split count S, workgroup width) and the K-order of every output element depend only on
@@ -122,7 +127,8 @@ hipError_t launch_gemm_skinny_norm_bf16(const uint16_t* X, const int32_t* row_id
                                         float* ss, int M, int N, int K, SkinnyPlan plan,
                                         hipStream_t st);
 // Decode gate/up GEMM with the SwiGLU epilogue: H[M][F] = bf16(silu(A W_g^T) *
-// (A W_u^T)), W_gate_up = [W_g; W_u] [2F][K]; plan = skinny_plan(2F, K) with S == 1.
+// (A W_u^T)), W_gate_up [2F][K] interleaved (launch_pack_gate_up);
+// plan = skinny_plan(2F, K) with S == 1.
 // h_tiled: H in tile order (for a down projection that reads it so).
 hipError_t launch_gemm_skinny_swiglu_bf16(const uint16_t* A, const uint16_t* W_gate_up,
                                           uint16_t* H, int M, int F, int K, SkinnyPlan plan,
@@ -132,81 +138,27 @@ hipError_t launch_gemm_skinny_swiglu_bf16(const uint16_t* A, const uint16_t* W_g
 // (tile_off); the other decode kernels read A row-major.
 bool skinny_reads_tiled(int N, int K, int M, bool fuse);
 
-// part[s][m][n] = sum_{k in slice s} A[m][k] * W[n][k] with 256 x 256 MFMA
-// tiles (prefill; K a multiple of 64 * S). S = tile_splits(N, K); the k
-// order is fixed and M-independent. The tile GEMMs read A in tile order
-// (tile_off; its buffer holds M rounded up to 16 rows) and write their bf16
-// activation outputs (SwiGLU and residual variants) in tile order.
-int tile_splits(int N, int K);
-hipError_t launch_gemm_tile_bf16(const uint16_t* A, const uint16_t* W, float* C, int M, int N,
-                                 int K, int S, hipStream_t st);
-// Epilogue inputs of the tile GEMM variants below (unused fields zero).
-struct TileEpiArgs {
-  // QKV variant
-  const int32_t* row_info = nullptr;  // [M][2] row slots from the gather kernel
-  const float* rope = nullptr;        // [rope_rows][64] (cos, sin) pairs
-  uint16_t* q_out = nullptr;
-  uint16_t* k_cache = nullptr;
-  uint16_t* v_cache = nullptr;
-  int Hq = 0, Hkv = 0;
-  // residual variant
-  const uint16_t* res_x = nullptr;    // residual rows [*][N] (bf16)
-  const int32_t* res_idx = nullptr;   // row m's residual row (null: m)
-  const uint16_t* gamma = nullptr;    // RMSNorm_2 gains [N]
-  float* ss_part = nullptr;           // [N / 256][M] per-tile row sums of x1^2
-  // SwiGLU variant with RMSNorm_2 folded in
-  const float* ss_in = nullptr;       // [n_ss][M] from the residual variant
-  int n_ss = 0, d = 0;
-  float eps = 0.f;
-};
-
-// Gate/up GEMM with the SwiGLU epilogue: H[M][F] = bf16(silu(A W_g^T) * (A W_u^T))
-// where W_gate_up = [W_g; W_u] is [2F][K]; only for tile_splits(2F, K) == 1.
-// With ss_in non-null (RMSNorm_2 folded in: A = bf16(x1 * gamma)), gate and
-// up of row m are first scaled by 1 / sqrt(sum_t ss_in[t][m] / K + eps),
-// t < ss_tiles (at most 32) in order.
-hipError_t launch_gemm_tile_swiglu_bf16(const uint16_t* A, const uint16_t* W_gate_up,
-                                        uint16_t* H, int M, int F, int K, const float* ss_in,
-                                        int ss_tiles, float eps, hipStream_t st);
-// Prefill QKV projection with the QKV epilogue in the GEMM's own epilogue
-// (head_dim 128): RoPE on query and key heads with the rotations of the RoPE
-// table, queries to q_out [M][Hq*128] in bf16, keys and values into the
-// paged cache tiles; no fp32 partials. Only when tile_qkv_fusable(Hq, Hkv, K).
-bool tile_qkv_fusable(int Hq, int Hkv, int K);
-hipError_t launch_gemm_tile_qkv_bf16(const uint16_t* A, const uint16_t* W_qkv, int M, int K,
-                                     const TileEpiArgs& ea, hipStream_t st);
-// Prefill O projection with the residual and the first half of RMSNorm_2 in
-// its epilogue: x1[m] = A W^T + res_x[res_idx ? res_idx[m] : m] (fp32),
-// h[m] = bf16(x1 * gamma), ss_part[t][m] = sum of x1^2 over columns
-// 256t .. 256t + 255. With tile_norm2_foldable(d, qdim, F), the O projection
-// (N = d, K = qdim) and the gate/up projection take this path.
-bool tile_norm2_foldable(int d, int qdim, int F);
-hipError_t launch_gemm_tile_resid_bf16(const uint16_t* A, const uint16_t* W, int M, int N, int K,
-                                       const uint16_t* res_x, const int32_t* res_idx,
-                                       const uint16_t* gamma, float* x1, uint16_t* h,
-                                       float* ss_part, hipStream_t st);
-
-// Narrow-output prefill GEMMs (N = the model width): 256 x TN tiles,
-// TN = narrow_tile_n(N) (128 or 160, N / TN <= 32 column tiles; 0: no plan),
-// unsplit along K (K a multiple of 128), A and W in tile order.
-int narrow_tile_n(int N);
-struct NarrowEpiArgs {
+// Prefill GEMMs (bf16, any M): A in tile order (tile_off; its buffer holds M
+// rounded up to 16 rows), W in tile order, N and K multiples of 128, unsplit
+// along K. The tile shape is chosen by (M, N, K) and the number of CUs and
+// changes no result. Epilogue inputs of the variants (unused fields zero):
+struct PrefillEpiArgs {
   // residual variant (O projection)
   const uint16_t* res_x = nullptr;   // residual rows [*][N] (bf16)
   const int32_t* res_idx = nullptr;  // row m's residual row (null: m)
   const uint16_t* gamma = nullptr;   // RMSNorm_2 gains [N]
   float* x1 = nullptr;               // [M][N] fp32
   uint16_t* h = nullptr;             // bf16(x1 * gamma), tile order
-  float* ss_part = nullptr;          // [N / TN][M] per-tile row sums of x1^2
+  float* ss_part = nullptr;          // [M][N / 32] row sums of x1^2 per 32 columns
   // scatter variant (down projection)
   const float* x1_in = nullptr;      // [M][N] fp32 residual
   uint16_t* out = nullptr;           // output rows [*][N] (bf16)
   const int32_t* out_idx = nullptr;  // row m's output row (null: m)
   // SwiGLU variant (gate/up projection, RMSNorm_2 folded in); h above is
   // its output [M][N / 2] in tile order
-  const float* ss_in = nullptr;      // [n_ss][M] from the residual variant
-  int n_ss = 0;
+  const float* ss_in = nullptr;      // [M][K / 32] from the residual variant
   float eps = 0.f;
+  bool h_rows = false;               // h row-major instead (SwiGLU without 1/rms only)
   // QKV variant (head_dim 128)
   const int32_t* row_info = nullptr;  // [M][2] row slots from the gather kernel
   const float* rope = nullptr;        // [rope_rows][64] (cos, sin) pairs
@@ -217,44 +169,36 @@ struct NarrowEpiArgs {
 };
 // O projection with the residual and the first half of RMSNorm_2 in its
 // epilogue: x1[m] = A W^T + res_x[res_idx ? res_idx[m] : m] (fp32),
-// h[m] = bf16(x1 * gamma) in tile order, ss_part[t][m] = sum of x1^2 over
-// columns TN t .. TN t + TN - 1, summed in a fixed order.
-hipError_t launch_gemm_narrow_resid_bf16(const uint16_t* A, const uint16_t* W, int M, int N,
-                                         int K, const uint16_t* res_x, const int32_t* res_idx,
-                                         const uint16_t* gamma, float* x1, uint16_t* h,
-                                         float* ss_part, hipStream_t st);
-// Gate/up projection with RMSNorm_2's 1/rms and the SwiGLU in its epilogue,
-// on 256 x 192 tiles (96 outputs each): H[m] = bf16(silu(g) * u) in tile
-// order [M][F], where (g, u) = (A W_g^T, A W_u^T)[m] / sqrt(sum_t ss_in[t][m]
-// / K + eps), t < ss_tiles (at most 32) in order, and W_gate_up = [W_g; W_u]
-// is [2F][K]. Only when narrow_swiglu_fits(F, K): 2F a multiple of 192.
-bool narrow_swiglu_fits(int F, int K);
-hipError_t launch_gemm_narrow_swiglu_bf16(const uint16_t* A, const uint16_t* W_gate_up,
-                                          uint16_t* H, int M, int F, int K, const float* ss_in,
-                                          int ss_tiles, float eps, hipStream_t st);
-// The same SwiGLU epilogue without the 1/rms (A already normalised), on
-// 256 x 128 tiles, for decode batches whose gate/up GEMM takes one round of
-// workgroups: narrow_swiglu_plain_fits(M, F, K). A is in tile order, H is
-// written in tile order [M][F]. Every output is the v_mfma_f32_16x16x32_bf16
-// chain over k in ascending 32-steps of the decode GEMMs, with the same
-// epilogue arithmetic, so the bits equal theirs.
-bool narrow_swiglu_plain_fits(int M, int F, int K);
-hipError_t launch_gemm_narrow_swiglu_plain_bf16(const uint16_t* A, const uint16_t* W_gate_up,
-                                                uint16_t* H, int M, int F, int K,
-                                                hipStream_t st);
-// Prefill QKV projection with RoPE and the cache append in its epilogue
-// (head_dim 128), on 256 x TN tiles that each hold TN/2 whole rotation pairs
-// (dims j and j + 64 of a head), TN = narrow_qkv_tile_n(Hq, Hkv, K) (224,
-// 192 or 160; 0: no plan): queries to q_out [M][Hq*128] in bf16, keys
-// (rotated) and values into the paged cache tiles.
-int narrow_qkv_tile_n(int Hq, int Hkv, int K);
-hipError_t launch_gemm_narrow_qkv_bf16(const uint16_t* A, const uint16_t* W_qkv, int M, int K,
-                                       const NarrowEpiArgs& ea, hipStream_t st);
+// h[m] = bf16(x1 * gamma) in tile order, ss_part[m][g] = sum of x1^2 over
+// columns 32g .. 32g + 31, in a fixed order.
+hipError_t launch_prefill_resid_bf16(const uint16_t* A, const uint16_t* W, int M, int N, int K,
+                                     const uint16_t* res_x, const int32_t* res_idx,
+                                     const uint16_t* gamma, float* x1, uint16_t* h,
+                                     float* ss_part, int num_cus, hipStream_t st);
+// Gate/up projection with RMSNorm_2's 1/rms and the SwiGLU in its epilogue:
+// H[m] = bf16(silu(g) * u) in tile order [M][F], where (g, u) = (A W_g^T,
+// A W_u^T)[m] / sqrt(sum_g ss_in[m][g] / K + eps), and W_gate_up [2F][K] is in
+// the interleaved order of launch_pack_gate_up.
+hipError_t launch_prefill_swiglu_bf16(const uint16_t* A, const uint16_t* W_gate_up, uint16_t* H,
+                                      int M, int F, int K, const float* ss_in, float eps,
+                                      int num_cus, hipStream_t st);
+// The same SwiGLU epilogue without the 1/rms (A already normalised), for
+// decode batches. Every output is the v_mfma_f32_16x16x32_bf16 chain over k in
+// ascending 32-steps of the decode GEMMs, with the same epilogue arithmetic,
+// so the bits equal theirs. h_tiled: H in tile order, else row-major.
+hipError_t launch_prefill_swiglu_plain_bf16(const uint16_t* A, const uint16_t* W_gate_up,
+                                            uint16_t* H, int M, int F, int K, bool h_tiled,
+                                            int num_cus, hipStream_t st);
+// QKV projection with RoPE and the cache append in its epilogue (head_dim
+// 128): queries to q_out [M][Hq*128] in bf16, keys (rotated) and values into
+// the paged cache tiles.
+hipError_t launch_prefill_qkv_bf16(const uint16_t* A, const uint16_t* W_qkv, int M, int K,
+                                   const PrefillEpiArgs& ea, int num_cus, hipStream_t st);
 // Down projection with the residual and the scatter in its epilogue:
 // out[out_idx ? out_idx[m] : m] = bf16(x1[m] + A W^T).
-hipError_t launch_gemm_narrow_scatter_bf16(const uint16_t* A, const uint16_t* W, int M, int N,
-                                           int K, const float* x1, uint16_t* out,
-                                           const int32_t* out_idx, hipStream_t st);
+hipError_t launch_prefill_scatter_bf16(const uint16_t* A, const uint16_t* W, int M, int N, int K,
+                                       const float* x1, uint16_t* out, const int32_t* out_idx,
+                                       int num_cus, hipStream_t st);
 
 // part[0][m][n] = sum_k A[m][k] * W[n][k], fp32 (tiny fp32 configurations).
 hipError_t launch_gemm_f32(const float* A, const float* W, float* part, int M, int N, int K,

@@ -522,9 +522,11 @@ __global__ __launch_bounds__(kRowThreads) void swiglu_kernel(const float* __rest
   const int c = 4 * (blockIdx.x * kRowThreads + threadIdx.x);
   if (c >= F) return;
   const int64_t pstride = (int64_t)M * 2 * F;
-  const float* p = part + (int64_t)i * 2 * F + c;
+  // bf16: 8 gate columns, then the 8 matching up columns (launch_pack_gate_up).
+  constexpr bool kPairs = std::is_same<T, bf16_t>::value;
+  const float* p = part + (int64_t)i * 2 * F + (kPairs ? 2 * c - (c & 7) : c);
   const f32x4_t g = sum_parts4<S>(p, pstride);
-  const f32x4_t up = sum_parts4<S>(p + F, pstride);
+  const f32x4_t up = sum_parts4<S>(p + (kPairs ? 8 : F), pstride);
   T* dst = u + (tiled ? tile_off(i, c, F) : (int64_t)i * F + c);
   float r[4];
 #pragma unroll
