@@ -24,7 +24,7 @@ FLAGS = ["-O3", "-std=c++17", f"--offload-arch={ARCH}", "-fPIC", "-Wall",
          "-Wno-unused-function", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          f"-I{os.path.join(ROOT, 'include')}"]
 SOURCES = ["rows.hip", "gemm_skinny.hip", "gemm_prefill_qkv.hip", "gemm_prefill_resid.hip",
-           "gemm_prefill_swiglu.hip", "gemm_prefill_scatter.hip", "attention.hip", "coco_api.hip",
+           "gemm_prefill_swiglu.hip", "gemm_prefill_scatter.hip", "attention.hip", "layer_f32.hip", "coco_api.hip",
            "probe.hip", "scaling.cpp"]
 
 

@@ -678,58 +678,6 @@ __global__ __launch_bounds__(WAVES * KS * 64, KS > 1 ? 1 : 8 / WAVES) void attn_
   }
 }
 
-// ---------------------------------------------------------------- fp32 path
-__global__ __launch_bounds__(64) void attn_f32_kernel(
-    const float* __restrict__ q, const float* __restrict__ k_cache,
-    const float* __restrict__ v_cache, const int32_t* __restrict__ block_table, int max_blocks,
-    const int32_t* __restrict__ ctx_lens, const int32_t* __restrict__ positions,
-    const int32_t* __restrict__ seq_starts, int n_seqs, int Hq, int Hkv, int hd,
-    float* __restrict__ o) {
-  const int i = blockIdx.x, h = blockIdx.y, lane = threadIdx.x;
-  const int s = row_to_seq(seq_starts, n_seqs, i);
-  const int g = h / (Hq / Hkv);
-  const int n = min(ctx_lens[s], positions[i] + 1);
-  const float scale = 1.0f / sqrtf((float)hd);
-  constexpr int kMaxPer = 4;  // hd <= 256
-  float qv[kMaxPer], acc[kMaxPer];
-#pragma unroll
-  for (int u = 0; u < kMaxPer; ++u) {
-    const int e = lane + u * 64;
-    qv[u] = e < hd ? q[((int64_t)i * Hq + h) * hd + e] : 0.f;
-    acc[u] = 0.f;
-  }
-  float m = -INFINITY, l = 0.f;
-  const int32_t* bt = block_table + (int64_t)s * max_blocks;
-  for (int t = 0; t < n; ++t) {
-    const int64_t blk = bt[t / kBlockTokens];
-    const int slot = t % kBlockTokens;
-    const float* kt = k_cache + (blk * Hkv + g) * kBlockTokens * hd;
-    const float* vt = v_cache + (blk * Hkv + g) * kBlockTokens * hd;
-    float d = 0.f;
-#pragma unroll
-    for (int u = 0; u < kMaxPer; ++u) {
-      const int e = lane + u * 64;
-      if (e < hd) d = fmaf(qv[u], kt[k_tile_offset(slot, e)], d);
-    }
-    const float z = wave_sum(d) * scale;
-    const float m_new = fmaxf(m, z);
-    const float alpha = expf(m - m_new), p = expf(z - m_new);
-    l = l * alpha + p;
-    m = m_new;
-#pragma unroll
-    for (int u = 0; u < kMaxPer; ++u) {
-      const int e = lane + u * 64;
-      if (e < hd)
-        acc[u] = acc[u] * alpha + p * vt[v_tile_offset(slot, e)];
-    }
-  }
-#pragma unroll
-  for (int u = 0; u < kMaxPer; ++u) {
-    const int e = lane + u * 64;
-    if (e < hd) o[((int64_t)i * Hq + h) * hd + e] = n > 0 ? acc[u] / l : 0.f;
-  }
-}
-
 }  // namespace
 
 int decode_max_splits(int max_blocks_per_seq) {
@@ -788,17 +736,6 @@ hipError_t launch_attn_prefill_bf16(const uint16_t* q, const uint16_t* k_cache,
                      dim3((unsigned)(tiles * Hq)), dim3(kPfLaunchWaves * kPfKeySets * 64), 0, st, q,
                      k_cache, v_cache, block_table, max_blocks, ctx_lens, positions, seq_starts,
                      n_seqs, Hq, Hkv, scale_log2, o);
-  return hipGetLastError();
-}
-
-hipError_t launch_attn_f32(const float* q, const float* k_cache, const float* v_cache,
-                           const int32_t* block_table, int max_blocks, const int32_t* ctx_lens,
-                           const int32_t* positions, const int32_t* seq_starts, int n_seqs,
-                           int n_rows, int Hq, int Hkv, int hd, float* o, hipStream_t st) {
-  if (n_rows <= 0) return hipSuccess;
-  COCO_LAUNCH(attn_f32_kernel, dim3(n_rows, Hq), dim3(64), 0, st, q, k_cache, v_cache,
-                     block_table, max_blocks, ctx_lens, positions, seq_starts, n_seqs, Hq, Hkv,
-                     hd, o);
   return hipGetLastError();
 }
 

@@ -595,35 +595,15 @@ int validate_batch(coco_layer* H, int64_t hidden_rows, const int32_t* row_idx, i
 // ----------------------------------------------------------------------------
 // Launch sequence.
 // ----------------------------------------------------------------------------
-// The GEMMs that write fp32 partials (decode and fp32; bf16 prefill GEMMs
-// finish their consumer's work instead). bf16: the weight-streaming plan
+// The decode GEMMs that write fp32 partials, on the weight-streaming plan
 // (split-K from (N, K) only).
-template <typename T>
-int gemm(float* part, const T* A, const T* W, int M, int N, int K, int* S, hipStream_t st);
-
-template <>
-int gemm<bf16_t>(float* part, const bf16_t* A, const bf16_t* W, int M, int N, int K, int* S,
-                 hipStream_t st) {
+int gemm(float* part, const bf16_t* A, const bf16_t* W, int M, int N, int K, int* S,
+         hipStream_t st) {
   const SkinnyPlan plan = skinny_plan(N, K);
   if (plan.waves == 0) return fail(COCO_EINVAL, "no GEMM plan for N=%d K=%d", N, K);
   *S = plan.S;
   HIPCHK(launch_gemm_skinny_bf16(A, W, part, M, N, K, plan, st));
   return COCO_OK;
-}
-
-template <>
-int gemm<float>(float* part, const float* A, const float* W, int M, int N, int K, int* S,
-                hipStream_t st) {
-  *S = 1;
-  HIPCHK(launch_gemm_f32(A, W, part, M, N, K, st));
-  return COCO_OK;
-}
-
-// Decode: SwiGLU runs in the gate/up GEMM's epilogue whenever that GEMM is not
-// split along K (bf16).
-template <typename T>
-bool fused_swiglu(int F, int K) {
-  return std::is_same<T, bf16_t>::value && skinny_plan(2 * F, K).S == 1;
 }
 
 // Decode: whether the (unsplit, bf16) gate/up projection of M rows runs on the
@@ -662,15 +642,9 @@ ActLayout act_layout(const coco_layer* H, bool prefill, int M) {
   return a;
 }
 
-template <typename T>
 int attention(coco_layer* H, const Work& W, const coco_layer_weights& w, int M,
               const int32_t* positions, const int32_t* seq_starts, int n_seqs, const int32_t* bt,
-              const int32_t* ctx, bool o_tiled, hipStream_t st);
-
-template <>
-int attention<bf16_t>(coco_layer* H, const Work& W, const coco_layer_weights& w, int M,
-                      const int32_t* positions, const int32_t* seq_starts, int n_seqs,
-                      const int32_t* bt, const int32_t* ctx, bool o_tiled, hipStream_t st) {
+              const int32_t* ctx, bool o_tiled, hipStream_t st) {
   const coco_layer_config& c = H->cfg;
   if (!seq_starts) {
     {
@@ -690,19 +664,6 @@ int attention<bf16_t>(coco_layer* H, const Work& W, const coco_layer_weights& w,
                                     positions, seq_starts, n_seqs, M, c.n_q_heads, c.n_kv_heads,
                                     (bf16_t*)W.o, st));
   }
-  return COCO_OK;
-}
-
-template <>
-int attention<float>(coco_layer* H, const Work& W, const coco_layer_weights& w, int M,
-                     const int32_t* positions, const int32_t* seq_starts, int n_seqs,
-                     const int32_t* bt, const int32_t* ctx, bool o_tiled, hipStream_t st) {
-  (void)o_tiled;  // fp32: row-major throughout
-  const coco_layer_config& c = H->cfg;
-  KernelTimer t(H, COCO_K_ATTENTION, st);
-  HIPCHK(launch_attn_f32((const float*)W.q, (const float*)w.k_cache, (const float*)w.v_cache,
-                         bt, c.max_blocks_per_seq, ctx, positions, seq_starts, n_seqs, M,
-                         c.n_q_heads, c.n_kv_heads, c.head_dim, (float*)W.o, st));
   return COCO_OK;
 }
 
@@ -726,8 +687,8 @@ int prefill_layer(coco_layer* H, const Work& W, const coco_layer_weights& w, con
   const int d = c.d_model, F = c.d_ffn, qd = c.n_q_heads * c.head_dim;
   bf16_t *h = (bf16_t*)W.h, *o = (bf16_t*)W.o, *h2 = (bf16_t*)W.h2, *u = (bf16_t*)W.u;
   TIMED(COCO_K_GATHER_NORM,
-        HIPCHK(launch_gather_rmsnorm<bf16_t>(x_src, x_idx, M, d, (const bf16_t*)w.gamma_attn,
-                                             c.rms_eps, nullptr, h, true, rs, st)));
+        HIPCHK(launch_gather_rmsnorm_bf16(x_src, x_idx, M, d, (const bf16_t*)w.gamma_attn,
+                                          c.rms_eps, h, rs, st)));
   PrefillEpiArgs qa;
   qa.row_info = W.row_info;
   qa.rope = H->rope;
@@ -739,7 +700,7 @@ int prefill_layer(coco_layer* H, const Work& W, const coco_layer_weights& w, con
   TIMED(COCO_K_GEMM_QKV,
         HIPCHK(launch_prefill_qkv_bf16(h, (const bf16_t*)w.w_qkv, M, d, qa, H->num_cus, st)));
   int rc;
-  if ((rc = attention<bf16_t>(H, W, w, M, positions, seq_starts, n_seqs, bt, ctx, true, st)))
+  if ((rc = attention(H, W, w, M, positions, seq_starts, n_seqs, bt, ctx, true, st)))
     return rc;
   float* const ss = W.part;
   TIMED(COCO_K_GEMM_O,
@@ -755,23 +716,119 @@ int prefill_layer(coco_layer* H, const Work& W, const coco_layer_weights& w, con
   return COCO_OK;
 }
 
+// One bf16 decode layer. The gather and RMSNorm_1 are folded into the QKV
+// projection: it stages bf16(x * gamma) straight from the input rows and the
+// QKV epilogue applies each row's 1/rms.
+int decode_layer(coco_layer* H, const Work& W, const coco_layer_weights& w, const bf16_t* x_src,
+                 const int32_t* x_idx, bf16_t* y, const int32_t* y_idx, int M,
+                 const int32_t* positions, const int32_t* bt, const int32_t* ctx,
+                 hipStream_t st) {
+  const coco_layer_config& c = H->cfg;
+  const int d = c.d_model, Hq = c.n_q_heads, Hkv = c.n_kv_heads, hd = c.head_dim, F = c.d_ffn;
+  const int nqkv = (Hq + 2 * Hkv) * hd;
+  const ActLayout lay = act_layout(H, false, M);
+  bf16_t *q = (bf16_t*)W.q, *o = (bf16_t*)W.o, *h2 = (bf16_t*)W.h2, *u = (bf16_t*)W.u;
+  int S, rc;
+  const SkinnyPlan plan = skinny_plan(nqkv, d);
+  if (plan.waves == 0) return fail(COCO_EINVAL, "no GEMM plan for N=%d K=%d", nqkv, d);
+  TIMED(COCO_K_GEMM_QKV,
+        HIPCHK(launch_gemm_skinny_norm_bf16(x_src, x_idx, (const bf16_t*)w.gamma_attn,
+                                            (const bf16_t*)w.w_qkv, W.part, W.ss, M, nqkv, d,
+                                            plan, st)));
+  // RoPE, local cache append.
+  TIMED(COCO_K_QKV_EPILOGUE,
+        HIPCHK(launch_qkv_epilogue<bf16_t>(W.part, plan.S, M, Hq, Hkv, hd, positions, nullptr, M,
+                                           bt, c.max_blocks_per_seq, H->inv_freq, q,
+                                           (bf16_t*)w.k_cache, (bf16_t*)w.v_cache, ctx,
+                                           W.split_off, H->max_splits, W.ss, d, c.rms_eps, st)));
+  // Attention over the paged cache.
+  if ((rc = attention(H, W, w, M, positions, nullptr, M, bt, ctx, lay.o, st))) return rc;
+  // O projection + residual + RMSNorm_2.
+  TIMED(COCO_K_GEMM_O,
+        if ((rc = gemm(W.part, o, (const bf16_t*)w.w_o, M, d, Hq * hd, &S, st))) return rc);
+  TIMED(COCO_K_RESIDUAL_NORM,
+        HIPCHK(launch_residual_rmsnorm<bf16_t>(W.part, S, M, d, x_src, x_idx,
+                                               (const bf16_t*)w.gamma_mlp, c.rms_eps, W.x1, h2,
+                                               lay.h2, st)));
+  // SwiGLU MLP: in the gate/up GEMM's epilogue whenever that GEMM is not split
+  // along K.
+  if (tile_swiglu(H, M)) {
+    TIMED(COCO_K_GEMM_GATE_UP,
+          HIPCHK(launch_prefill_swiglu_plain_bf16(h2, (const bf16_t*)w.w_gate_up, u, M, F, d,
+                                                  lay.u, H->num_cus, st)));
+  } else if (skinny_plan(2 * F, d).S == 1) {
+    TIMED(COCO_K_GEMM_GATE_UP,
+          HIPCHK(launch_gemm_skinny_swiglu_bf16(h2, (const bf16_t*)w.w_gate_up, u, M, F, d,
+                                                skinny_plan(2 * F, d), lay.u, st)));
+  } else {
+    TIMED(COCO_K_GEMM_GATE_UP,
+          if ((rc = gemm(W.part, h2, (const bf16_t*)w.w_gate_up, M, 2 * F, d, &S, st))) return rc);
+    TIMED(COCO_K_SWIGLU, HIPCHK(launch_swiglu<bf16_t>(W.part, S, M, F, u, lay.u, st)));
+  }
+  // Down projection and residual.
+  TIMED(COCO_K_GEMM_DOWN,
+        if ((rc = gemm(W.part, u, (const bf16_t*)w.w_down, M, d, F, &S, st))) return rc);
+  TIMED(COCO_K_RESIDUAL_SCATTER,
+        HIPCHK(launch_residual_scatter<bf16_t>(W.part, S, M, d, W.x1, y, y_idx, st)));
+  return COCO_OK;
+}
+
+// One fp32 layer, decode and prefill alike: five kernels.
+int f32_layer(coco_layer* H, const Work& W, const coco_layer_weights& w, const float* x_src,
+              const int32_t* x_idx, float* y, const int32_t* y_idx, int M,
+              const int32_t* positions, const int32_t* seq_starts, int n_seqs, const int32_t* bt,
+              const int32_t* ctx, hipStream_t st) {
+  const coco_layer_config& c = H->cfg;
+  const int d = c.d_model, Hq = c.n_q_heads, Hkv = c.n_kv_heads, hd = c.head_dim, F = c.d_ffn;
+  F32EpiArgs qa;
+  qa.gamma = (const float*)w.gamma_attn;
+  qa.eps = c.rms_eps;
+  qa.h = (float*)W.h;
+  qa.row_idx = x_idx;
+  qa.positions = positions;
+  qa.seq_starts = seq_starts;
+  qa.block_table = bt;
+  qa.inv_freq = H->inv_freq;
+  qa.q_out = (float*)W.q;
+  qa.k_cache = (float*)w.k_cache;
+  qa.v_cache = (float*)w.v_cache;
+  qa.n_seqs = n_seqs;
+  qa.max_blocks = c.max_blocks_per_seq;
+  qa.Hq = Hq;
+  qa.Hkv = Hkv;
+  qa.hd = hd;
+  TIMED(COCO_K_GEMM_QKV, HIPCHK(launch_f32_qkv(x_src, (const float*)w.w_qkv, M, d, qa, st)));
+  TIMED(COCO_K_ATTENTION,
+        HIPCHK(launch_attn_f32((const float*)W.q, (const float*)w.k_cache,
+                               (const float*)w.v_cache, bt, c.max_blocks_per_seq, ctx, positions,
+                               seq_starts, n_seqs, M, Hq, Hkv, hd, (float*)W.o, st)));
+  F32EpiArgs oa;
+  oa.row_idx = x_idx;
+  oa.res = x_src;
+  oa.out = W.x1;
+  TIMED(COCO_K_GEMM_O,
+        HIPCHK(launch_f32_resid((const float*)W.o, (const float*)w.w_o, M, d, Hq * hd, oa, st)));
+  F32EpiArgs ga;
+  ga.gamma = (const float*)w.gamma_mlp;
+  ga.eps = c.rms_eps;
+  ga.h = (float*)W.h2;
+  ga.out = (float*)W.u;
+  TIMED(COCO_K_GEMM_GATE_UP,
+        HIPCHK(launch_f32_swiglu(W.x1, (const float*)w.w_gate_up, M, F, d, ga, st)));
+  F32EpiArgs da;
+  da.row_idx = y_idx;
+  da.res = W.x1;
+  da.out = y;
+  TIMED(COCO_K_GEMM_DOWN,
+        HIPCHK(launch_f32_scatter((const float*)W.u, (const float*)w.w_down, M, d, F, da, st)));
+  return COCO_OK;
+}
+
 template <typename T>
 int run_span(coco_layer* H, const Work& W, int first, int nl, T* hidden, const int32_t* row_idx,
              int M, const int32_t* positions, const int32_t* seq_starts, int n_seqs,
              const int32_t* bt, const int32_t* ctx, hipStream_t st) {
-  const coco_layer_config& c = H->cfg;
-  const int d = c.d_model, Hq = c.n_q_heads, Hkv = c.n_kv_heads, hd = c.head_dim, F = c.d_ffn;
-  const int nqkv = (Hq + 2 * Hkv) * hd;
-  constexpr bool kBf16 = std::is_same<T, bf16_t>::value;
   T* x = (T*)W.x;
-  T* h = (T*)W.h;
-  T* q = (T*)W.q;
-  T* o = (T*)W.o;
-  T* h2 = (T*)W.h2;
-  T* u = (T*)W.u;
-  int S, rc;
-  const bool pre = seq_starts != nullptr;
-  const ActLayout lay = act_layout(H, pre, M);
   for (int l = first; l < first + nl; ++l) {
     const coco_layer_weights& w = H->layers[l];
     const bool first_l = l == first, last_l = l == first + nl - 1;
@@ -782,83 +839,29 @@ int run_span(coco_layer* H, const Work& W, int first, int nl, T* hidden, const i
     const int32_t* x_idx = first_l ? row_idx : nullptr;
     T* const y = last_l ? hidden : x;
     const int32_t* y_idx = last_l ? row_idx : nullptr;
-    // Prefill row slots (position, cache block), written once per call by the
-    // first layer's gather.
-    RowSlotArgs rs;
-    if constexpr (kBf16) {
-      if (pre) {
-        if (first_l) {
-          rs.positions = positions;
-          rs.seq_starts = seq_starts;
-          rs.block_table = bt;
-          rs.row_info = W.row_info;
-          rs.n_seqs = n_seqs;
-          rs.max_blocks = c.max_blocks_per_seq;
-          rs.rope_rows = H->rope_rows;
-        }
-        if ((rc = prefill_layer(H, W, w, x_src, x_idx, y, y_idx, M, positions, seq_starts,
-                                n_seqs, bt, ctx, rs, st)))
-          return rc;
-        continue;
-      }
-      // Decode folds the gather and RMSNorm_1 into the QKV projection: it
-      // stages bf16(x * gamma) straight from the input rows and the QKV
-      // epilogue applies each row's 1/rms.
-      const SkinnyPlan plan = skinny_plan(nqkv, d);
-      if (plan.waves == 0) return fail(COCO_EINVAL, "no GEMM plan for N=%d K=%d", nqkv, d);
-      S = plan.S;
-      TIMED(COCO_K_GEMM_QKV,
-            HIPCHK(launch_gemm_skinny_norm_bf16((const bf16_t*)x_src, x_idx,
-                                                (const bf16_t*)w.gamma_attn,
-                                                (const bf16_t*)w.w_qkv, W.part, W.ss, M, nqkv, d,
-                                                plan, st)));
+    int rc;
+    if constexpr (std::is_same<T, float>::value) {
+      rc = f32_layer(H, W, w, x_src, x_idx, y, y_idx, M, positions, seq_starts, n_seqs, bt, ctx,
+                     st);
+    } else if (seq_starts == nullptr) {
+      rc = decode_layer(H, W, w, x_src, x_idx, y, y_idx, M, positions, bt, ctx, st);
     } else {
-      // fp32: a gather + RMSNorm_1 kernel writes h first.
-      TIMED(COCO_K_GATHER_NORM,
-            HIPCHK(launch_gather_rmsnorm<T>(x_src, x_idx, M, d, (const T*)w.gamma_attn,
-                                            c.rms_eps, nullptr, h, false, rs, st)));
-      TIMED(COCO_K_GEMM_QKV,
-            if ((rc = gemm<T>(W.part, h, (const T*)w.w_qkv, M, nqkv, d, &S, st))) return rc);
-    }
-    // RoPE, local cache append.
-    TIMED(COCO_K_QKV_EPILOGUE,
-          HIPCHK(launch_qkv_epilogue<T>(W.part, S, M, Hq, Hkv, hd, positions, seq_starts, n_seqs,
-                                        bt, c.max_blocks_per_seq, H->inv_freq, q, (T*)w.k_cache,
-                                        (T*)w.v_cache, ctx, kBf16 ? W.split_off : nullptr,
-                                        H->max_splits, kBf16 ? W.ss : nullptr, d, c.rms_eps,
-                                        st)));
-    // Attention over the paged cache.
-    if ((rc = attention<T>(H, W, w, M, positions, seq_starts, n_seqs, bt, ctx, lay.o, st)))
-      return rc;
-    // O projection + residual + RMSNorm_2.
-    TIMED(COCO_K_GEMM_O,
-          if ((rc = gemm<T>(W.part, o, (const T*)w.w_o, M, d, Hq * hd, &S, st))) return rc);
-    TIMED(COCO_K_RESIDUAL_NORM,
-          HIPCHK(launch_residual_rmsnorm<T>(W.part, S, M, d, x_src, x_idx, (const T*)w.gamma_mlp,
-                                            c.rms_eps, W.x1, h2, lay.h2, st)));
-    // SwiGLU MLP.
-    if (fused_swiglu<T>(F, d)) {
-      if (tile_swiglu(H, M)) {
-        TIMED(COCO_K_GEMM_GATE_UP,
-              HIPCHK(launch_prefill_swiglu_plain_bf16((const uint16_t*)h2,
-                                                      (const uint16_t*)w.w_gate_up, (uint16_t*)u,
-                                                      M, F, d, lay.u, H->num_cus, st)));
-      } else {
-        TIMED(COCO_K_GEMM_GATE_UP,
-              HIPCHK(launch_gemm_skinny_swiglu_bf16((const bf16_t*)h2,
-                                                    (const bf16_t*)w.w_gate_up, (bf16_t*)u, M, F,
-                                                    d, skinny_plan(2 * F, d), lay.u, st)));
+      // Prefill row slots (position, cache block), written once per call by
+      // the first layer's gather.
+      RowSlotArgs rs;
+      if (first_l) {
+        rs.positions = positions;
+        rs.seq_starts = seq_starts;
+        rs.block_table = bt;
+        rs.row_info = W.row_info;
+        rs.n_seqs = n_seqs;
+        rs.max_blocks = H->cfg.max_blocks_per_seq;
+        rs.rope_rows = H->rope_rows;
       }
-    } else {
-      TIMED(COCO_K_GEMM_GATE_UP,
-            if ((rc = gemm<T>(W.part, h2, (const T*)w.w_gate_up, M, 2 * F, d, &S, st))) return rc);
-      TIMED(COCO_K_SWIGLU, HIPCHK(launch_swiglu<T>(W.part, S, M, F, u, lay.u, st)));
+      rc = prefill_layer(H, W, w, x_src, x_idx, y, y_idx, M, positions, seq_starts, n_seqs, bt,
+                         ctx, rs, st);
     }
-    // Down projection and residual.
-    TIMED(COCO_K_GEMM_DOWN,
-          if ((rc = gemm<T>(W.part, u, (const T*)w.w_down, M, d, F, &S, st))) return rc);
-    TIMED(COCO_K_RESIDUAL_SCATTER,
-          HIPCHK(launch_residual_scatter<T>(W.part, S, M, d, W.x1, y, y_idx, st)));
+    if (rc) return rc;
   }
   return COCO_OK;
 }

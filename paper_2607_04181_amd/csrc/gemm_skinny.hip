@@ -654,38 +654,4 @@ hipError_t launch_pack_gate_up(const uint16_t* W, int F, int K, uint16_t* out, h
   return pack(W, 2LL * F, K, F, out, st);
 }
 
-// ----------------------------------------------------------------------------
-// fp32 GEMM for the tiny fp32 configuration: 16x16 LDS tiles, k ascending.
-// ----------------------------------------------------------------------------
-namespace {
-__global__ __launch_bounds__(256) void gemm_f32_kernel(const float* __restrict__ A,
-                                                       const float* __restrict__ W,
-                                                       float* __restrict__ out, int M, int N,
-                                                       int K) {
-  __shared__ float as[16][17], ws[16][17];
-  const int tx = threadIdx.x & 15, ty = threadIdx.x >> 4;
-  const int m = blockIdx.y * 16 + ty, n = blockIdx.x * 16 + tx;
-  float acc = 0.f;
-  for (int k0 = 0; k0 < K; k0 += 16) {
-    const int am = blockIdx.y * 16 + ty, ak = k0 + tx;
-    as[ty][tx] = (am < M && ak < K) ? A[(int64_t)am * K + ak] : 0.f;
-    const int wn = blockIdx.x * 16 + ty;
-    ws[ty][tx] = (wn < N && ak < K) ? W[(int64_t)wn * K + ak] : 0.f;
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < 16; ++kk) acc = fmaf(as[ty][kk], ws[tx][kk], acc);
-    __syncthreads();
-  }
-  if (m < M && n < N) out[(int64_t)m * N + n] = acc;
-}
-}  // namespace
-
-hipError_t launch_gemm_f32(const float* A, const float* W, float* part, int M, int N, int K,
-                           hipStream_t st) {
-  if (M <= 0) return hipSuccess;
-  COCO_LAUNCH(gemm_f32_kernel, dim3((N + 15) / 16, (M + 15) / 16), dim3(256), 0, st, A,
-                     W, part, M, N, K);
-  return hipGetLastError();
-}
-
 }  // namespace coco

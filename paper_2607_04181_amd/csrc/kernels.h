@@ -35,14 +35,11 @@ struct RowSlotArgs {
   int n_seqs = 0, max_blocks = 0, rope_rows = 0;
 };
 
-// x_out[i] = src[row_idx ? row_idx[i] : i];  h_out[i] = RMSNorm(x) * gamma.
-// x_out may be null (span layers after the first read x in place).
-// tiled (bf16 prefill): h_out in tile order (tile_off), the prefill GEMM's A
-// operand layout; otherwise row-major.
-template <typename T>
-hipError_t launch_gather_rmsnorm(const T* src, const int32_t* row_idx, int M, int d,
-                                 const T* gamma, float eps, T* x_out, T* h_out, bool tiled,
-                                 const RowSlotArgs& rs, hipStream_t st);
+// h_out[i] = RMSNorm(src[row_idx ? row_idx[i] : i]) * gamma, in tile order
+// (tile_off), the prefill GEMM's A operand layout; and the rows' slots.
+hipError_t launch_gather_rmsnorm_bf16(const uint16_t* src, const int32_t* row_idx, int M, int d,
+                                      const uint16_t* gamma, float eps, uint16_t* h_out,
+                                      const RowSlotArgs& rs, hipStream_t st);
 
 // RoPE table rope[p][j] = (cos, sin)(p * inv_freq[j]) for p < n_pos and
 // j < half, angle and both functions in fp64 (as the QKV epilogue computes
@@ -73,8 +70,8 @@ hipError_t launch_residual_rmsnorm(const float* part, int S, int M, int d, const
                                    const int32_t* row_idx, const T* gamma, float eps, float* x1,
                                    T* h2, bool tiled, hipStream_t st);
 
-// u = silu(sum_s gate) * sum_s up, part rows [2F] = gate then up (fp32) or in
-// the interleaved order of launch_pack_gate_up (bf16). tiled: u in tile order.
+// u = silu(sum_s gate) * sum_s up, part rows [2F] in the interleaved order of
+// launch_pack_gate_up. tiled: u in tile order.
 template <typename T>
 hipError_t launch_swiglu(const float* part, int S, int M, int F, T* u, bool tiled,
                          hipStream_t st);
@@ -200,9 +197,41 @@ hipError_t launch_prefill_scatter_bf16(const uint16_t* A, const uint16_t* W, int
                                        const float* x1, uint16_t* out, const int32_t* out_idx,
                                        int num_cus, hipStream_t st);
 
-// part[0][m][n] = sum_k A[m][k] * W[n][k], fp32 (tiny fp32 configurations).
-hipError_t launch_gemm_f32(const float* A, const float* W, float* part, int M, int N, int K,
-                           hipStream_t st);
+// ---------------------------------------------------------------- fp32 layer
+// The four GEMMs of an fp32 layer (row-major, nn.Linear weights; K a multiple
+// of 4), with the layer's row work in their prologues and epilogues. Epilogue
+// inputs (unused fields zero):
+struct F32EpiArgs {
+  const float* gamma = nullptr;       // QKV, SwiGLU: RMSNorm gains [K]
+  float eps = 0.f;
+  float* h = nullptr;                 // QKV, SwiGLU: the normalised rows [M][K]
+  const int32_t* row_idx = nullptr;   // QKV: row m's source row; residual: its row of res;
+                                      // scatter: its row of out (null: m)
+  const float* res = nullptr;         // residual, scatter: what is added
+  float* out = nullptr;               // residual: x1 [M][N]; SwiGLU: u [M][F]; scatter: rows [*][N]
+  // QKV
+  const int32_t* positions = nullptr;
+  const int32_t* seq_starts = nullptr;
+  const int32_t* block_table = nullptr;
+  const double* inv_freq = nullptr;
+  float* q_out = nullptr;
+  float* k_cache = nullptr;
+  float* v_cache = nullptr;
+  int n_seqs = 0, max_blocks = 0, Hq = 0, Hkv = 0, hd = 0;
+};
+// RMSNorm_1, QKV projection, RoPE, queries to q_out [M][Hq*hd], keys and
+// values into the paged cache.
+hipError_t launch_f32_qkv(const float* x, const float* w_qkv, int M, int d, const F32EpiArgs& ea,
+                          hipStream_t st);
+// out[m] = res[row_idx[m]] + o[m] W_o^T.
+hipError_t launch_f32_resid(const float* o, const float* w_o, int M, int d, int qd,
+                            const F32EpiArgs& ea, hipStream_t st);
+// RMSNorm_2, gate/up projection ([2F][d]: gate rows, then up rows), SwiGLU.
+hipError_t launch_f32_swiglu(const float* x1, const float* w_gate_up, int M, int F, int d,
+                             const F32EpiArgs& ea, hipStream_t st);
+// out[row_idx[m]] = res[m] + u[m] W_down^T.
+hipError_t launch_f32_scatter(const float* u, const float* w_down, int M, int d, int F,
+                              const F32EpiArgs& ea, hipStream_t st);
 
 // ---------------------------------------------------------------- attention
 constexpr int kDecodeSplit = 256;  // tokens per split-KV partition
@@ -236,7 +265,7 @@ hipError_t launch_attn_prefill_bf16(const uint16_t* q, const uint16_t* k_cache,
                                     int n_seqs, int n_rows, int Hq, int Hkv, uint16_t* o,
                                     hipStream_t st);
 
-// fp32 path: one wave per (row, query head), decode and prefill alike.
+// fp32 path, decode and prefill alike (hd a multiple of 32, at most 256).
 hipError_t launch_attn_f32(const float* q, const float* k_cache, const float* v_cache,
                            const int32_t* block_table, int max_blocks,
                            const int32_t* ctx_lens, const int32_t* positions,

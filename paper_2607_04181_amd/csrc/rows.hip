@@ -1,4 +1,4 @@
-// Row-wise kernels of the decoder layer: gather + RMSNorm, the epilogues that
+// Row-wise kernels of the bf16 decoder layer: gather + RMSNorm, the epilogues that
 // reduce split-K partials of the projections (RoPE + cache append, residual +
 // RMSNorm, SwiGLU, residual + scatter) and the paged key/value append.
 //
@@ -64,45 +64,8 @@ __device__ __forceinline__ u32x4_t pack_bf16x8(const float* f) {
 // ----------------------------------------------------------------------------
 // Prefill row slots: row_info[i] = (position clamped to the RoPE table,
 // cache block of the position), for the QKV projection's fused epilogue.
-__device__ __forceinline__ void write_row_slot(const RowSlotArgs& rs, int i) {
-  const int pos = rs.positions[i];
-  int lo = 0, hi = rs.n_seqs - 1;  // the s with seq_starts[s] <= i < seq_starts[s + 1]
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (rs.seq_starts[mid] <= i) lo = mid; else hi = mid - 1;
-  }
-  const int blk = rs.block_table[(int64_t)lo * rs.max_blocks +
-                                 min(max(pos, 0) / kBlockTokens, rs.max_blocks - 1)];
-  rs.row_info[2 * i] = min(max(pos, 0), rs.rope_rows - 1);
-  rs.row_info[2 * i + 1] = blk;
-}
-
-template <typename T>
-__global__ __launch_bounds__(kRowThreads) void gather_rmsnorm_kernel(
-    const T* __restrict__ src, const int32_t* __restrict__ row_idx, int d,
-    const T* __restrict__ gamma, float eps, T* __restrict__ x_out, T* __restrict__ h_out,
-    bool tiled, RowSlotArgs rs) {
-  (void)tiled;  // bf16 only
-  __shared__ float red[kRowThreads / kWave];
-  const int i = blockIdx.x;
-  if (rs.row_info != nullptr && threadIdx.x == 0) write_row_slot(rs, i);
-  const int64_t r = row_idx ? (int64_t)row_idx[i] : (int64_t)i;
-  const T* x = src + r * d;
-  float ss = 0.f;
-  for (int c = threadIdx.x; c < d; c += kRowThreads) {
-    const float v = Elem<T>::load(x + c);
-    ss += v * v;
-    if (x_out) x_out[(int64_t)i * d + c] = x[c];
-  }
-  ss = block_sum<kRowThreads>(ss, red);
-  const float inv = 1.0f / sqrtf(ss / (float)d + eps);
-  for (int c = threadIdx.x; c < d; c += kRowThreads)
-    Elem<T>::store(h_out + (int64_t)i * d + c,
-                   Elem<T>::load(x + c) * inv * Elem<T>::load(gamma + c));
-}
-
 // bf16 rows, d % 8 == 0: 16-byte vectors, row held in registers.
-//   * Row of a workgroup: with `tiled`, consecutive rows run on one XCD
+//   * Row of a workgroup: consecutive rows run on one XCD
 //     (blockIdx % 8 is the XCD), so the 16 rows that share each 1 KB
 //     tile-order block fill it in that XCD's L2 and it leaves as whole lines;
 //   * the row slot (prefill QKV epilogue) is found by the first wave with
@@ -134,13 +97,12 @@ __device__ __forceinline__ void write_row_slot_uniform(const RowSlotArgs& rs, in
 template <int NV>
 __global__ __launch_bounds__(kRowThreads) void gather_rmsnorm_bf16_kernel(
     const bf16_t* __restrict__ src, const int32_t* __restrict__ row_idx, int d,
-    const bf16_t* __restrict__ gamma, float eps, bf16_t* __restrict__ x_out,
-    bf16_t* __restrict__ h_out, bool tiled, RowSlotArgs rs) {
+    const bf16_t* __restrict__ gamma, float eps, bf16_t* __restrict__ h_out, RowSlotArgs rs) {
   __shared__ float red[kRowThreads / kWave];
   constexpr int kXCDs = 8;
   const int nb = gridDim.x, b = blockIdx.x;
   const int full = (nb / kXCDs) * kXCDs;
-  const int i = tiled && b < full ? (b % kXCDs) * (nb / kXCDs) + b / kXCDs : b;
+  const int i = b < full ? (b % kXCDs) * (nb / kXCDs) + b / kXCDs : b;
   const int64_t r = row_idx ? (int64_t)row_idx[i] : (int64_t)i;
   const int nv = d / 8;
   const u32x4_t* x = (const u32x4_t*)(src + r * d);
@@ -163,7 +125,6 @@ __global__ __launch_bounds__(kRowThreads) void gather_rmsnorm_bf16_kernel(
       unpack_bf16x8(xv[u], f);
 #pragma unroll
       for (int e = 0; e < 8; ++e) ss += f[e] * f[e];
-      if (x_out) ((u32x4_t*)(x_out + (int64_t)i * d))[v] = xv[u];
     }
   }
   ss = block_sum<kRowThreads>(ss, red);
@@ -177,37 +138,29 @@ __global__ __launch_bounds__(kRowThreads) void gather_rmsnorm_bf16_kernel(
       unpack_bf16x8(gv[u], gf);
 #pragma unroll
       for (int e = 0; e < 8; ++e) f[e] = f[e] * inv * gf[e];
-      *(u32x4_t*)(h_out + (tiled ? tile_off(i, 8 * v, d) : (int64_t)i * d + 8 * v)) =
-          pack_bf16x8(f);
+      *(u32x4_t*)(h_out + tile_off(i, 8 * v, d)) = pack_bf16x8(f);
     }
   }
 }
 
-template <typename T>
-hipError_t launch_gather_rmsnorm(const T* src, const int32_t* row_idx, int M, int d,
-                                 const T* gamma, float eps, T* x_out, T* h_out, bool tiled,
-                                 const RowSlotArgs& rs, hipStream_t st) {
+hipError_t launch_gather_rmsnorm_bf16(const bf16_t* src, const int32_t* row_idx, int M, int d,
+                                      const bf16_t* gamma, float eps, bf16_t* h_out,
+                                      const RowSlotArgs& rs, hipStream_t st) {
   if (M <= 0) return hipSuccess;
   if (rs.row_info != nullptr && (rs.n_seqs < 1 || rs.max_blocks < 1 || rs.rope_rows < 1))
     return hipErrorInvalidValue;
-  if (tiled && (!std::is_same<T, bf16_t>::value || d % 32 != 0)) return hipErrorInvalidValue;
-  if constexpr (std::is_same<T, bf16_t>::value) {
-    if (d % 8 != 0 || d > 8 * kRowThreads * 8) return hipErrorInvalidValue;
-    const int nvt = (d / 8 + kRowThreads - 1) / kRowThreads;  // vectors per thread, 1..8
-    switch (nvt) {
+  if (d % 32 != 0 || d > 8 * kRowThreads * 8) return hipErrorInvalidValue;
+  const int nvt = (d / 8 + kRowThreads - 1) / kRowThreads;  // vectors per thread, 1..8
+  switch (nvt) {
 #define COCO_GN_CASE(n)                                                                       \
   case n:                                                                                     \
     COCO_LAUNCH(gather_rmsnorm_bf16_kernel<n>, dim3(M), dim3(kRowThreads), 0, st, src,         \
-                row_idx, d, gamma, eps, x_out, h_out, tiled, rs);                             \
+                row_idx, d, gamma, eps, h_out, rs);                                           \
     break;
-      COCO_GN_CASE(1) COCO_GN_CASE(2) COCO_GN_CASE(3) COCO_GN_CASE(4)
-      COCO_GN_CASE(5) COCO_GN_CASE(6) COCO_GN_CASE(7) COCO_GN_CASE(8)
+    COCO_GN_CASE(1) COCO_GN_CASE(2) COCO_GN_CASE(3) COCO_GN_CASE(4)
+    COCO_GN_CASE(5) COCO_GN_CASE(6) COCO_GN_CASE(7) COCO_GN_CASE(8)
 #undef COCO_GN_CASE
-      default: return hipErrorInvalidValue;
-    }
-  } else {
-    COCO_LAUNCH(gather_rmsnorm_kernel<T>, dim3(M), dim3(kRowThreads), 0, st, src, row_idx, d,
-                gamma, eps, x_out, h_out, tiled, rs);
+    default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
 }
@@ -522,11 +475,10 @@ __global__ __launch_bounds__(kRowThreads) void swiglu_kernel(const float* __rest
   const int c = 4 * (blockIdx.x * kRowThreads + threadIdx.x);
   if (c >= F) return;
   const int64_t pstride = (int64_t)M * 2 * F;
-  // bf16: 8 gate columns, then the 8 matching up columns (launch_pack_gate_up).
-  constexpr bool kPairs = std::is_same<T, bf16_t>::value;
-  const float* p = part + (int64_t)i * 2 * F + (kPairs ? 2 * c - (c & 7) : c);
+  // 8 gate columns, then the 8 matching up columns (launch_pack_gate_up).
+  const float* p = part + (int64_t)i * 2 * F + 2 * c - (c & 7);
   const f32x4_t g = sum_parts4<S>(p, pstride);
-  const f32x4_t up = sum_parts4<S>(p + (kPairs ? 8 : F), pstride);
+  const f32x4_t up = sum_parts4<S>(p + 8, pstride);
   T* dst = u + (tiled ? tile_off(i, c, F) : (int64_t)i * F + c);
   float r[4];
 #pragma unroll
@@ -636,26 +588,23 @@ hipError_t launch_kv_append(const T* k, const T* v, const int32_t* seq_idx,
   return hipGetLastError();
 }
 
-#define COCO_INSTANTIATE(T)                                                                   \
-  template hipError_t launch_gather_rmsnorm<T>(const T*, const int32_t*, int, int, const T*, \
-                                               float, T*, T*, bool, const RowSlotArgs&,      \
-                                               hipStream_t);                                 \
-  template hipError_t launch_qkv_epilogue<T>(const float*, int, int, int, int, int,          \
-                                             const int32_t*, const int32_t*, int,            \
-                                             const int32_t*, int, const double*, T*, T*, T*, \
-                                             const int32_t*, int32_t*, int, const float*,    \
-                                             int, float, hipStream_t);                       \
-  template hipError_t launch_residual_rmsnorm<T>(const float*, int, int, int, const T*,      \
-                                                 const int32_t*, const T*, float, float*, T*, \
-                                                 bool, hipStream_t);                         \
-  template hipError_t launch_swiglu<T>(const float*, int, int, int, T*, bool, hipStream_t);  \
-  template hipError_t launch_residual_scatter<T>(const float*, int, int, int, const float*,  \
-                                                 T*, const int32_t*, hipStream_t);           \
-  template hipError_t launch_kv_append<T>(const T*, const T*, const int32_t*, const int32_t*, \
-                                          int, int, int, const int32_t*, int, T*, T*,        \
+template hipError_t launch_qkv_epilogue<bf16_t>(const float*, int, int, int, int, int,
+                                                const int32_t*, const int32_t*, int,
+                                                const int32_t*, int, const double*, bf16_t*,
+                                                bf16_t*, bf16_t*, const int32_t*, int32_t*, int,
+                                                const float*, int, float, hipStream_t);
+template hipError_t launch_residual_rmsnorm<bf16_t>(const float*, int, int, int, const bf16_t*,
+                                                    const int32_t*, const bf16_t*, float, float*,
+                                                    bf16_t*, bool, hipStream_t);
+template hipError_t launch_swiglu<bf16_t>(const float*, int, int, int, bf16_t*, bool,
                                           hipStream_t);
-
-COCO_INSTANTIATE(bf16_t)
-COCO_INSTANTIATE(float)
+template hipError_t launch_residual_scatter<bf16_t>(const float*, int, int, int, const float*,
+                                                    bf16_t*, const int32_t*, hipStream_t);
+template hipError_t launch_kv_append<bf16_t>(const bf16_t*, const bf16_t*, const int32_t*,
+                                             const int32_t*, int, int, int, const int32_t*, int,
+                                             bf16_t*, bf16_t*, hipStream_t);
+template hipError_t launch_kv_append<float>(const float*, const float*, const int32_t*,
+                                            const int32_t*, int, int, int, const int32_t*, int,
+                                            float*, float*, hipStream_t);
 
 }  // namespace coco
