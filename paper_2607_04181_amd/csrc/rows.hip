@@ -556,24 +556,143 @@ hipError_t launch_residual_scatter(const float* part, int S, int M, int d, const
 }
 
 // ----------------------------------------------------------------------------
-// Paged key/value append (bit copy into the tile layout).
+// Paged key/value append (bit copy into the tile layout), bound by the bytes
+// moved. A workgroup takes 16 consecutive tokens of one head through LDS, so
+// that loads run along a token's dims and stores along the tile: 8 dims of a
+// key per piece, tokens side by side; for values the tile interleaves four
+// tokens, and a piece of 2 dims x 4 tokens is stored whole where four
+// consecutive tokens of the call fill slots 4a .. 4a + 3 of one block (the
+// run's first token stores for all four, also those of the next workgroup's
+// tokens), other tokens element by element. One 2-byte store per element ran
+// at 1.9 TB/s (6000 tokens of 8 heads x 128, 49 MB read and written: 26.5 us);
+// 14.7 now, of
+// which a loop of calls needs 13.3 on the host alone. (Runs found per workgroup
+// by one ballot: with every wave looking them up token by token in LDS, it
+// stayed at 27 whatever the stores.)
 // ----------------------------------------------------------------------------
+constexpr int kApTok = 16;    // tokens of a workgroup
+constexpr int kApHalo = 3;    // tokens before and after it that share its runs
+
 template <typename T>
+struct alignas(16) Piece8 {
+  T e[8];
+};
+
+// HD: head_dim (0: hd_arg).
+template <typename T, int HD>
 __global__ __launch_bounds__(kRowThreads) void kv_append_kernel(
     const T* __restrict__ k, const T* __restrict__ v, const int32_t* __restrict__ seq_idx,
-    const int32_t* __restrict__ positions, int Hkv, int hd,
-    const int32_t* __restrict__ block_table, int max_blocks, T* __restrict__ k_cache,
-    T* __restrict__ v_cache) {
-  const int t = blockIdx.x;
-  const int pos = positions[t];
-  const int64_t blk = block_table[(int64_t)seq_idx[t] * max_blocks + pos / kBlockTokens];
-  const int slot = pos % kBlockTokens;
-  const int64_t src = (int64_t)t * Hkv * hd;
-  for (int e = threadIdx.x; e < Hkv * hd; e += kRowThreads) {
-    const int h = e / hd, dim = e - h * hd;
-    const int64_t tile = (blk * Hkv + h) * kBlockTokens * hd;
-    k_cache[tile + k_tile_offset(slot, dim)] = k[src + e];
-    v_cache[tile + v_tile_offset(slot, dim)] = v[src + e];
+    const int32_t* __restrict__ positions, int n, int Hkv, int hd_arg,
+    const int32_t* __restrict__ block_table, int max_blocks, bool aligned,
+    T* __restrict__ k_cache, T* __restrict__ v_cache) {
+  constexpr int kMaxHd = HD ? HD : 256;
+  const int hd = HD ? HD : hd_arg;
+  constexpr int kPad = 16 / sizeof(T);  // row padding: key pieces of 16 rows on distinct banks
+  constexpr int kInfo = kApTok + 2 * kApHalo;
+  __shared__ __attribute__((aligned(16))) T ks[kApTok * (kMaxHd + kPad)];
+  __shared__ __attribute__((aligned(16))) T vs[(kApTok + kApHalo) * (kMaxHd + kPad)];
+  __shared__ int64_t blk_s[kInfo];  // cache block and slot of tokens t0 - 3 .. t0 + 18
+  __shared__ int slot_s[kInfo];     // (-1: no such token)
+  __shared__ int lead[kApTok / 4], n_lead, lone;  // runs' first tokens; tokens of no run (bits)
+  // Consecutive windows on one XCD (blockIdx % 8), so that a tile shared by two
+  // windows fills up in that XCD's L2 and leaves as whole lines.
+  constexpr int kXCDs = 8;
+  const int nb = gridDim.x, b = blockIdx.x, full = (nb / kXCDs) * kXCDs;
+  const int lid = b < full ? (b % kXCDs) * (nb / kXCDs) + b / kXCDs : b;
+  const int t0 = lid / Hkv * kApTok, h = lid % Hkv;
+  const int stride = hd + kPad, pieces = hd / 8;
+  const int live = min(kApTok, n - t0), live_v = min(kApTok + kApHalo, n - t0);
+  // The index loads first: their chain runs while the rows are on their way.
+  const int ti = t0 - kApHalo + threadIdx.x;
+  const bool info = threadIdx.x < kInfo && ti >= 0 && ti < n;
+  int pos = 0, seq = 0;
+  if (info) {
+    pos = positions[ti];
+    seq = seq_idx[ti];
+  }
+  constexpr int kPer = ((kApTok + kApHalo) * (kMaxHd / 8) + kRowThreads - 1) / kRowThreads;
+  Piece8<T> kr[kPer], vr[kPer];
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    const int i = threadIdx.x + u * kRowThreads;
+    if (i >= live_v * pieces) continue;
+    const int t = i / pieces, c = i - t * pieces;
+    const int64_t src = ((int64_t)(t0 + t) * Hkv + h) * hd + 8 * c;
+    if (aligned) {
+      if (t < live) kr[u] = *(const Piece8<T>*)(k + src);
+      vr[u] = *(const Piece8<T>*)(v + src);
+    } else {  // the inputs are not 16-byte aligned
+      for (int e = 0; e < 8; ++e) {
+        if (t < live) kr[u].e[e] = k[src + e];
+        vr[u].e[e] = v[src + e];
+      }
+    }
+  }
+  if (threadIdx.x < kInfo) {
+    blk_s[threadIdx.x] =
+        info ? block_table[(int64_t)seq * max_blocks + pos / kBlockTokens] : -1;
+    slot_s[threadIdx.x] = info ? pos % kBlockTokens : -1;
+  }
+#pragma unroll
+  for (int u = 0; u < kPer; ++u) {
+    const int i = threadIdx.x + u * kRowThreads;
+    if (i >= live_v * pieces) continue;
+    const int t = i / pieces, c = i - t * pieces;
+    if (t < live) *(Piece8<T>*)(ks + t * stride + 8 * c) = kr[u];
+    *(Piece8<T>*)(vs + t * stride + 8 * c) = vr[u];
+  }
+  __syncthreads();
+  // Whether token t0 + i (i from -3) starts a run: slot 4a, and the next three
+  // tokens of the call in slots 4a + 1 .. 4a + 3 of the same block.
+  auto leads = [&](int i) -> bool {
+    const int x = i + kApHalo;
+    if (x < 0 || x + 3 >= kInfo || slot_s[x] < 0 || slot_s[x] % 4 != 0) return false;
+    bool run = true;
+#pragma unroll
+    for (int e = 1; e < 4; ++e)
+      run = run && slot_s[x + e] == slot_s[x] + e && blk_s[x + e] == blk_s[x];
+    return run;
+  };
+  if (threadIdx.x < kWave) {
+    const bool l = threadIdx.x < live && leads(threadIdx.x);
+    const uint64_t mask = __ballot(l);
+    if (l) lead[__popcll(mask & ((1ull << threadIdx.x) - 1))] = threadIdx.x;
+    const int x = min((int)threadIdx.x, live - 1);
+    const uint64_t none =
+        __ballot(threadIdx.x < live && !leads(x - slot_s[x + kApHalo] % 4));
+    if (threadIdx.x == 0) {
+      n_lead = __popcll(mask);
+      lone = (int)none;
+    }
+  }
+  __syncthreads();
+  const int64_t tile_elems = (int64_t)kBlockTokens * hd;
+  for (int i = threadIdx.x; i < kApTok * pieces; i += kRowThreads) {
+    const int t = i % kApTok, c = i / kApTok;
+    if (t >= live) continue;
+    T* tile = k_cache + (blk_s[t + kApHalo] * Hkv + h) * tile_elems;
+    *(Piece8<T>*)(tile + k_tile_offset(slot_s[t + kApHalo], 8 * c)) =
+        *(const Piece8<T>*)(ks + t * stride + 8 * c);
+  }
+  // Runs: piece (dims d and d + 16 of a 32-dim group, four tokens).
+  const int per_run = hd / 2;
+  for (int i = threadIdx.x; i < n_lead * per_run; i += kRowThreads) {
+    const int t = lead[i / per_run], x = i % per_run;
+    const int d = (x >> 4) * 32 + (x & 15);
+    Piece8<T> y;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      y.e[e] = vs[(t + e) * stride + d];
+      y.e[4 + e] = vs[(t + e) * stride + d + 16];
+    }
+    T* tile = v_cache + (blk_s[t + kApHalo] * Hkv + h) * tile_elems;
+    *(Piece8<T>*)(tile + v_tile_offset(slot_s[t + kApHalo], d)) = y;
+  }
+  for (int rest = lone; rest != 0; rest &= rest - 1) {
+    const int t = __ffs(rest) - 1;
+    T* tile = v_cache + (blk_s[t + kApHalo] * Hkv + h) * tile_elems;
+    for (int d = threadIdx.x; d < hd; d += kRowThreads)
+      tile[v_tile_offset(slot_s[t + kApHalo], d)] = vs[t * stride + d];
   }
 }
 
@@ -583,8 +702,18 @@ hipError_t launch_kv_append(const T* k, const T* v, const int32_t* seq_idx,
                             const int32_t* block_table, int max_blocks, T* k_cache,
                             T* v_cache, hipStream_t st) {
   if (n <= 0) return hipSuccess;
-  COCO_LAUNCH(kv_append_kernel<T>, dim3(n), dim3(kRowThreads), 0, st, k, v, seq_idx,
-                     positions, Hkv, hd, block_table, max_blocks, k_cache, v_cache);
+  if (hd % 32 != 0 || hd > 256) return hipErrorInvalidValue;
+  const bool aligned = ((uintptr_t)k | (uintptr_t)v) % 16 == 0;
+  const int64_t wgs = (int64_t)((n - 1) / kApTok + 1) * Hkv;
+  if (wgs > 0x7fffffff) return hipErrorInvalidValue;
+  if (hd == 128)
+    COCO_LAUNCH((kv_append_kernel<T, 128>), dim3((unsigned)wgs), dim3(kRowThreads), 0, st, k, v,
+                seq_idx, positions, n, Hkv, hd, block_table, max_blocks, aligned, k_cache,
+                v_cache);
+  else
+    COCO_LAUNCH((kv_append_kernel<T, 0>), dim3((unsigned)wgs), dim3(kRowThreads), 0, st, k, v,
+                seq_idx, positions, n, Hkv, hd, block_table, max_blocks, aligned, k_cache,
+                v_cache);
   return hipGetLastError();
 }
 
