@@ -239,7 +239,7 @@ enum {
                      its rows from the hidden buffer) */
   COCO_WS_H = 1,  /* RMSNorm_1 output, [max_rows][d], dtype (prefill and
                      fp32 calls; bf16 decode folds RMSNorm_1 into the QKV
-                     projection and never writes it) */
+                     projection: not its contents) */
   COCO_WS_Q = 2,  /* rotated queries, [max_rows][Hq*hd], dtype */
   COCO_WS_O = 3,  /* attention output, [max_rows][Hq*hd], dtype */
   COCO_WS_X1 = 4, /* residual after the O projection, [max_rows][d], fp32 */

@@ -24,8 +24,8 @@ FLAGS = ["-O3", "-std=c++17", f"--offload-arch={ARCH}", "-fPIC", "-Wall",
          "-Wno-unused-function", "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
          f"-I{os.path.join(ROOT, 'include')}"]
 SOURCES = ["rows.hip", "gemm_skinny.hip", "gemm_prefill_qkv.hip", "gemm_prefill_resid.hip",
-           "gemm_prefill_swiglu.hip", "gemm_prefill_scatter.hip", "attention.hip", "layer_f32.hip", "coco_api.hip",
-           "probe.hip", "scaling.cpp"]
+           "gemm_prefill_swiglu.hip", "gemm_prefill_scatter.hip", "gemm_prefill_partial.hip",
+           "attention.hip", "layer_f32.hip", "coco_api.hip", "probe.hip", "scaling.cpp"]
 
 
 def build(verbose: bool = False, jobs: int = 8) -> str:

@@ -595,35 +595,66 @@ int validate_batch(coco_layer* H, int64_t hidden_rows, const int32_t* row_idx, i
 // ----------------------------------------------------------------------------
 // Launch sequence.
 // ----------------------------------------------------------------------------
-// The decode GEMMs that write fp32 partials, on the weight-streaming plan
-// (split-K from (N, K) only).
-int gemm(float* part, const bf16_t* A, const bf16_t* W, int M, int N, int K, int* S,
-         hipStream_t st) {
+// Which kernel a decode projection of M rows runs: the weight-streaming one
+// (skinny_plan: split-K from (N, K) only), or the prefill tile kernel on the
+// same K-slices, with the same bits.
+//   * Above 128 rows the skinny kernel reads the weights twice (us, skinny /
+//     tiles): 8B O 160 rows 25.5 / 13.5, 32B down 160 rows 136 / 79, 70B QKV
+//     200 rows 120 / 55 + 8 for its operand.
+//   * 4- and 8-wave plans of one full round: 64- and 128-column tiles make the
+//     same round. 8B O 1 row 10.7 / 7.6, 64 rows 12.1 / 9.4, 128 rows 16.3 /
+//     12.3; 8B down 64 rows 27.4 / 26.5; 70B O 64 rows 31.8 / 29.0, 70B down
+//     128 rows 102 / 97, 1 row 82.6 / 82.2. (8-wave plans of another grid:
+//     above 64 rows, where the skinny kernel stages 128.)
+//   * The rest stay: 32B O (5 waves) 64 rows 15.4 / 16.3, down 128 rows 74 / 80.
+bool tile_partial(const coco_layer* H, int N, int K, int M) {
+  const SkinnyPlan p = skinny_plan(N, K);
+  if (p.waves == 0) return false;
+  const bool round = N / (16 * p.waves) * p.S == H->num_cus;
+  return M > 128 || (round && (p.waves == 4 || p.waves == 8)) || (M > 64 && p.waves == 8);
+}
+
+// QKV: the tile kernel needs gather_scale's operand first (4-8 us), which the
+// skinny kernel folds in, so it pays where the weights are large too. 70B (84 M
+// weights) 65 rows 57 / 42 + 7, 128 rows 62 / 50 + 7; 32B (37 M) 128 rows 26.5 /
+// 22.7 + 4.6, 8B (25 M) 96 rows 20.4 / 17.0 + 4.2.
+bool tile_qkv(const coco_layer* H, int M) {
+  const coco_layer_config& c = H->cfg;
+  const int64_t N = (int64_t)(c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim;
+  return M > 128 || (M > 64 && N * c.d_model >= (64 << 20));
+}
+
+// The decode GEMMs that write fp32 partials.
+int gemm(const coco_layer* H, float* part, const bf16_t* A, const bf16_t* W, int M, int N, int K,
+         int* S, hipStream_t st) {
   const SkinnyPlan plan = skinny_plan(N, K);
   if (plan.waves == 0) return fail(COCO_EINVAL, "no GEMM plan for N=%d K=%d", N, K);
   *S = plan.S;
-  HIPCHK(launch_gemm_skinny_bf16(A, W, part, M, N, K, plan, st));
+  if (tile_partial(H, N, K, M))
+    HIPCHK(launch_tile_partial_bf16(A, W, part, M, N, K, plan.S, H->num_cus, st));
+  else
+    HIPCHK(launch_gemm_skinny_bf16(A, W, part, M, N, K, plan, st));
   return COCO_OK;
 }
 
 // Decode: whether the (unsplit, bf16) gate/up projection of M rows runs on the
-// prefill tile kernel: above 128 rows, where the skinny kernel reads the
-// weights twice, and above 64 where a grid of 128 x 256 tiles fills at least
-// three quarters of the CUs. Measured, skinny kernel against tiles (us): 8B
-// 128 rows 56.2 / 55.9, 160 rows 74.4 / 65.0, 400 rows 154 / 89; 32B (216
-// tiles) 65 rows 121 / 106, 128 rows 135 / 116; 70B (224 tiles) 80 rows 186 /
-// 176, 128 rows 200 / 177, 256 rows 310 / 210. 8B (112 such tiles) 80 rows
-// 49.3 / 51.6, and at 64 rows 45.4 / 46.5 (70B 172 / 174): those stay.
+// tile kernel: above 128 rows, and above 64 for 8-wave plans and where a grid
+// of 128 x 256 tiles fills at least three quarters of the CUs. Measured, skinny
+// kernel against tiles (us): 8B 128 rows 56.2 / 55.9, 160 rows 74.4 / 65.0, 400
+// rows 154 / 89; 32B (216 tiles) 65 rows 121 / 106, 128 rows 135 / 116; 70B
+// (224 tiles) 80 rows 186 / 176, 128 rows 200 / 177, 256 rows 310 / 210. 8B
+// (112 such tiles, 7 waves) 80 rows 49.3 / 51.6, and at 64 rows 45.4 / 46.5
+// (70B 172 / 174): those stay.
 bool tile_swiglu(const coco_layer* H, int M) {
   const int F = H->cfg.d_ffn;
-  return (M > 128 || (M > 64 && 2 * F / 256 >= H->num_cus * 3 / 4)) &&
-         skinny_plan(2 * F, H->cfg.d_model).S == 1;
+  const SkinnyPlan p = skinny_plan(2 * F, H->cfg.d_model);
+  return p.S == 1 &&
+         (M > 128 || (M > 64 && (p.waves == 8 || 2 * F / 256 >= H->num_cus * 3 / 4)));
 }
 
 // Layout of the four projections' A operands in a call: tile order
 // (tile_off) wherever the consuming GEMM reads it so -- every bf16 prefill
-// GEMM, and the decode GEMMs that run the row-split or the tile kernel -- else
-// row-major.
+// GEMM, and the decode GEMMs that run the tile kernel -- else row-major.
 struct ActLayout {
   bool h = false, o = false, h2 = false, u = false;
 };
@@ -636,9 +667,9 @@ ActLayout act_layout(const coco_layer* H, bool prefill, int M) {
     return a;
   }
   const int d = c.d_model, F = c.d_ffn, qd = c.n_q_heads * c.head_dim;
-  a.o = skinny_reads_tiled(d, qd, M, false);
-  a.h2 = tile_swiglu(H, M) || skinny_reads_tiled(2 * F, d, M, skinny_plan(2 * F, d).S == 1);
-  a.u = skinny_reads_tiled(d, F, M, false);
+  a.o = tile_partial(H, d, qd, M);
+  a.h2 = skinny_plan(2 * F, d).S == 1 ? tile_swiglu(H, M) : tile_partial(H, 2 * F, d, M);
+  a.u = tile_partial(H, d, F, M);
   return a;
 }
 
@@ -717,8 +748,9 @@ int prefill_layer(coco_layer* H, const Work& W, const coco_layer_weights& w, con
 }
 
 // One bf16 decode layer. The gather and RMSNorm_1 are folded into the QKV
-// projection: it stages bf16(x * gamma) straight from the input rows and the
-// QKV epilogue applies each row's 1/rms.
+// projection: its operand is bf16(x * gamma), staged straight from the input
+// rows (large batches: written by a kernel of its own), and the QKV epilogue
+// applies each row's 1/rms.
 int decode_layer(coco_layer* H, const Work& W, const coco_layer_weights& w, const bf16_t* x_src,
                  const int32_t* x_idx, bf16_t* y, const int32_t* y_idx, int M,
                  const int32_t* positions, const int32_t* bt, const int32_t* ctx,
@@ -731,10 +763,19 @@ int decode_layer(coco_layer* H, const Work& W, const coco_layer_weights& w, cons
   int S, rc;
   const SkinnyPlan plan = skinny_plan(nqkv, d);
   if (plan.waves == 0) return fail(COCO_EINVAL, "no GEMM plan for N=%d K=%d", nqkv, d);
-  TIMED(COCO_K_GEMM_QKV,
-        HIPCHK(launch_gemm_skinny_norm_bf16(x_src, x_idx, (const bf16_t*)w.gamma_attn,
-                                            (const bf16_t*)w.w_qkv, W.part, W.ss, M, nqkv, d,
-                                            plan, st)));
+  if (tile_qkv(H, M)) {
+    TIMED(COCO_K_GATHER_NORM,
+          HIPCHK(launch_gather_scale_bf16(x_src, x_idx, M, d, (const bf16_t*)w.gamma_attn,
+                                          (bf16_t*)W.h, W.ss, plan.S, st)));
+    TIMED(COCO_K_GEMM_QKV,
+          HIPCHK(launch_tile_partial_bf16((const bf16_t*)W.h, (const bf16_t*)w.w_qkv, W.part, M,
+                                          nqkv, d, plan.S, H->num_cus, st)));
+  } else {
+    TIMED(COCO_K_GEMM_QKV,
+          HIPCHK(launch_gemm_skinny_norm_bf16(x_src, x_idx, (const bf16_t*)w.gamma_attn,
+                                              (const bf16_t*)w.w_qkv, W.part, W.ss, M, nqkv, d,
+                                              plan, st)));
+  }
   // RoPE, local cache append.
   TIMED(COCO_K_QKV_EPILOGUE,
         HIPCHK(launch_qkv_epilogue<bf16_t>(W.part, plan.S, M, Hq, Hkv, hd, positions, nullptr, M,
@@ -745,7 +786,7 @@ int decode_layer(coco_layer* H, const Work& W, const coco_layer_weights& w, cons
   if ((rc = attention(H, W, w, M, positions, nullptr, M, bt, ctx, lay.o, st))) return rc;
   // O projection + residual + RMSNorm_2.
   TIMED(COCO_K_GEMM_O,
-        if ((rc = gemm(W.part, o, (const bf16_t*)w.w_o, M, d, Hq * hd, &S, st))) return rc);
+        if ((rc = gemm(H, W.part, o, (const bf16_t*)w.w_o, M, d, Hq * hd, &S, st))) return rc);
   TIMED(COCO_K_RESIDUAL_NORM,
         HIPCHK(launch_residual_rmsnorm<bf16_t>(W.part, S, M, d, x_src, x_idx,
                                                (const bf16_t*)w.gamma_mlp, c.rms_eps, W.x1, h2,
@@ -762,12 +803,12 @@ int decode_layer(coco_layer* H, const Work& W, const coco_layer_weights& w, cons
                                                 skinny_plan(2 * F, d), lay.u, st)));
   } else {
     TIMED(COCO_K_GEMM_GATE_UP,
-          if ((rc = gemm(W.part, h2, (const bf16_t*)w.w_gate_up, M, 2 * F, d, &S, st))) return rc);
+          if ((rc = gemm(H, W.part, h2, (const bf16_t*)w.w_gate_up, M, 2 * F, d, &S, st))) return rc);
     TIMED(COCO_K_SWIGLU, HIPCHK(launch_swiglu<bf16_t>(W.part, S, M, F, u, lay.u, st)));
   }
   // Down projection and residual.
   TIMED(COCO_K_GEMM_DOWN,
-        if ((rc = gemm(W.part, u, (const bf16_t*)w.w_down, M, d, F, &S, st))) return rc);
+        if ((rc = gemm(H, W.part, u, (const bf16_t*)w.w_down, M, d, F, &S, st))) return rc);
   TIMED(COCO_K_RESIDUAL_SCATTER,
         HIPCHK(launch_residual_scatter<bf16_t>(W.part, S, M, d, W.x1, y, y_idx, st)));
   return COCO_OK;

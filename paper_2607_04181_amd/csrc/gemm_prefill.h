@@ -19,7 +19,9 @@
 //     factors of an output sit 8 lanes apart; h = silu(gate / rms) * up / rms
 //     in tile order;
 //   * QKV: a tile holds whole RoPE pairs; queries are rotated into q, keys
-//     rotated and values copied into the paged cache.
+//     rotated and values copied into the paged cache;
+//   * partial (decode batches): the fp32 sums of K-slice blockIdx.y, for the
+//     decode epilogues.
 // Main loop:
 //   * WM x WN waves; each owns a TM/WM x TN/WN sub-tile as accumulators of
 //     16 x 16;
@@ -52,7 +54,7 @@ typedef __attribute__((address_space(3))) void lds_void_t;
 
 // kSwigluPlain: the SwiGLU epilogue without RMSNorm_2's 1/rms (the operand is
 // already normalised).
-enum { kResid = 0, kScatter = 1, kSwiglu = 2, kQkv = 3, kSwigluPlain = 4 };
+enum { kResid = 0, kScatter = 1, kSwiglu = 2, kQkv = 3, kSwigluPlain = 4, kPartial = 5 };
 
 // Tile shape: TM x TN outputs, WM x WN waves, KS 32-k blocks per stage,
 // SLOTS ring slots.
@@ -198,7 +200,9 @@ __global__ __launch_bounds__(T::NT) void gemm_prefill_kernel(const bf16_t* __res
   // the A blocks (row group, 32-k step), then the W blocks (column block,
   // 32-k step). Row groups past the last row read the last group; their rows
   // are never stored.
-  const int stages = K / (32 * KS);
+  const int k_slice = MODE == kPartial ? K / (int)gridDim.y : K;
+  const int stages = k_slice / (32 * KS);
+  const int64_t k_off = MODE == kPartial ? (int64_t)blockIdx.y * (k_slice / 32) * 1024 : 0;
   const char* src[LOADS];
 #pragma unroll
   for (int i = 0; i < LOADS; ++i) {
@@ -207,7 +211,7 @@ __global__ __launch_bounds__(T::NT) void gemm_prefill_kernel(const bf16_t* __res
     const int qq = a ? q : q - AB;
     const int blk = a ? min((m0 >> 4) + qq / KS, (M - 1) >> 4) : w_block(qq / KS);
     src[i] = (const char*)(a ? A : W) + ((int64_t)blk * (K / 32) + qq % KS) * 1024 +
-             (t & 3) * 256 + lane * T::bytes(i);
+             k_off + (t & 3) * 256 + lane * T::bytes(i);
   }
   // Loads past the last stage repeat it (never multiplied).
   auto issue = [&](int st, int slot) {
@@ -346,6 +350,22 @@ __global__ __launch_bounds__(T::NT) void gemm_prefill_kernel(const bf16_t* __res
   // slot; the 4-float pad spreads the four rows a wave store touches over
   // all banks), then every thread takes 8-column pieces of those rows, so
   // each load and store is 16 contiguous bytes per lane.
+  if constexpr (MODE == kPartial) {
+    // Lane (j4, c16) of block (i, j): rows 16 (RB wm + i) + 4 j4 + r, column
+    // 16 (CB wn + j) + c16. Non-temporal: read once, by the next kernel.
+    float* const out = ea.x1 + (int64_t)blockIdx.y * M * N;
+#pragma unroll
+    for (int i = 0; i < RB; ++i)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int m = m0 + 16 * (RB * wm + i) + 4 * j4 + r;
+        if (m >= M) continue;
+        float* const row = out + (int64_t)m * N + n0 + 16 * CB * wn + c16;
+#pragma unroll
+        for (int j = 0; j < CB; ++j) __builtin_nontemporal_store(acc[i][j][r], row + 16 * j);
+      }
+    return;
+  }
   __syncthreads();  // every wave is done with the ring
   if (tid < TM) {
     if constexpr (MODE == kQkv) {
@@ -849,37 +869,38 @@ enum TileId {
   k256x224, k256x192, k256x160, k256x128, k128x256, k128x160, k128x128, k128x64, k64x160,
   k64x128, k64x64, k64x32, k32x32, kTileCount
 };
-// The shape for an [M] x [N] x [K] product; -1 if none divides N.
-int choose_tile(int M, int N, int K, int num_cus);
+// The shape for an [M] x [N] x [K] product, run as S products of K / S; -1 if
+// none divides N.
+int choose_tile(int M, int N, int K, int S, int num_cus);
 
 template <class T, int MODE>
 hipError_t launch_one(const uint16_t* A, const uint16_t* W, int M, int N, int K,
-                      const PrefillEpiArgs& ea, hipStream_t st) {
-  if (N % T::TN != 0 || K % (32 * T::KS) != 0) return hipErrorInvalidValue;
+                      int S, const PrefillEpiArgs& ea, hipStream_t st) {
+  if (N % T::TN != 0 || S < 1 || K % (32 * T::KS * S) != 0) return hipErrorInvalidValue;
   const int64_t grid = (int64_t)((M + T::TM - 1) / T::TM) * (N / T::TN);
   if (grid > 0x7fffffff) return hipErrorInvalidValue;
-  COCO_LAUNCH((gemm_prefill_kernel<T, MODE>), dim3((unsigned)grid), dim3(T::NT), 0, st,
+  COCO_LAUNCH((gemm_prefill_kernel<T, MODE>), dim3((unsigned)grid, S), dim3(T::NT), 0, st,
               (const bf16_t*)A, (const bf16_t*)W, M, N, K, ea);
   return hipGetLastError();
 }
 
 template <int MODE>
-hipError_t launch_mode(const uint16_t* A, const uint16_t* W, int M, int N, int K,
+hipError_t launch_mode(const uint16_t* A, const uint16_t* W, int M, int N, int K, int S,
                        const PrefillEpiArgs& ea, int num_cus, hipStream_t st) {
-  switch (choose_tile(M, N, K, num_cus)) {
-    case k256x224: return launch_one<T256x224, MODE>(A, W, M, N, K, ea, st);
-    case k256x192: return launch_one<T256x192, MODE>(A, W, M, N, K, ea, st);
-    case k256x160: return launch_one<T256x160, MODE>(A, W, M, N, K, ea, st);
-    case k256x128: return launch_one<T256x128, MODE>(A, W, M, N, K, ea, st);
-    case k128x256: return launch_one<T128x256, MODE>(A, W, M, N, K, ea, st);
-    case k128x160: return launch_one<T128x160, MODE>(A, W, M, N, K, ea, st);
-    case k128x128: return launch_one<T128x128, MODE>(A, W, M, N, K, ea, st);
-    case k128x64: return launch_one<T128x64, MODE>(A, W, M, N, K, ea, st);
-    case k64x160: return launch_one<T64x160, MODE>(A, W, M, N, K, ea, st);
-    case k64x128: return launch_one<T64x128, MODE>(A, W, M, N, K, ea, st);
-    case k64x64: return launch_one<T64x64, MODE>(A, W, M, N, K, ea, st);
-    case k64x32: return launch_one<T64x32, MODE>(A, W, M, N, K, ea, st);
-    case k32x32: return launch_one<T32x32, MODE>(A, W, M, N, K, ea, st);
+  switch (choose_tile(M, N, K, S, num_cus)) {
+    case k256x224: return launch_one<T256x224, MODE>(A, W, M, N, K, S, ea, st);
+    case k256x192: return launch_one<T256x192, MODE>(A, W, M, N, K, S, ea, st);
+    case k256x160: return launch_one<T256x160, MODE>(A, W, M, N, K, S, ea, st);
+    case k256x128: return launch_one<T256x128, MODE>(A, W, M, N, K, S, ea, st);
+    case k128x256: return launch_one<T128x256, MODE>(A, W, M, N, K, S, ea, st);
+    case k128x160: return launch_one<T128x160, MODE>(A, W, M, N, K, S, ea, st);
+    case k128x128: return launch_one<T128x128, MODE>(A, W, M, N, K, S, ea, st);
+    case k128x64: return launch_one<T128x64, MODE>(A, W, M, N, K, S, ea, st);
+    case k64x160: return launch_one<T64x160, MODE>(A, W, M, N, K, S, ea, st);
+    case k64x128: return launch_one<T64x128, MODE>(A, W, M, N, K, S, ea, st);
+    case k64x64: return launch_one<T64x64, MODE>(A, W, M, N, K, S, ea, st);
+    case k64x32: return launch_one<T64x32, MODE>(A, W, M, N, K, S, ea, st);
+    case k32x32: return launch_one<T32x32, MODE>(A, W, M, N, K, S, ea, st);
     default: return hipErrorInvalidValue;
   }
 }

@@ -8,8 +8,8 @@ hipError_t launch_prefill_qkv_bf16(const uint16_t* A, const uint16_t* W_qkv, int
   if (M <= 0) return hipSuccess;
   if (!ea.row_info || !ea.rope || !ea.q_out || !ea.k_cache || !ea.v_cache)
     return hipErrorInvalidValue;
-  return prefill::launch_mode<prefill::kQkv>(A, W_qkv, M, (ea.Hq + 2 * ea.Hkv) * 128, K, ea,
-                                             num_cus, st);
+  return prefill::launch_mode<prefill::kQkv>(A, W_qkv, M, (ea.Hq + 2 * ea.Hkv) * 128, K, 1,
+                                             ea, num_cus, st);
 }
 
 }  // namespace coco

@@ -16,7 +16,7 @@ hipError_t launch_prefill_resid_bf16(const uint16_t* A, const uint16_t* W, int M
   ea.x1 = x1;
   ea.h = h;
   ea.ss_part = ss_part;
-  return prefill::launch_mode<prefill::kResid>(A, W, M, N, K, ea, num_cus, st);
+  return prefill::launch_mode<prefill::kResid>(A, W, M, N, K, 1, ea, num_cus, st);
 }
 
 }  // namespace coco

@@ -12,7 +12,7 @@ hipError_t launch_prefill_scatter_bf16(const uint16_t* A, const uint16_t* W, int
   ea.x1_in = x1;
   ea.out = out;
   ea.out_idx = out_idx;
-  return prefill::launch_mode<prefill::kScatter>(A, W, M, N, K, ea, num_cus, st);
+  return prefill::launch_mode<prefill::kScatter>(A, W, M, N, K, 1, ea, num_cus, st);
 }
 
 }  // namespace coco

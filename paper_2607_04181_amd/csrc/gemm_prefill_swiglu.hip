@@ -21,7 +21,7 @@ namespace prefill {
 // shape for every M: 8B, 300 rows: QKV 69 -> 30 us, O 43 -> 24, down 124 ->
 // 70; 32B, 512 rows, down 379 -> 212; 70B, 1,000 rows, O 187 -> 113 (256 x 256
 // tiles before).
-int choose_tile(int M, int N, int K, int num_cus) {
+int choose_tile(int M, int N, int K, int S, int num_cus) {
   struct Shape {
     int tm, tn, steps, per_cu;  // steps in flight, workgroups per CU
   };
@@ -38,14 +38,14 @@ int choose_tile(int M, int N, int K, int num_cus) {
   for (int t = 0; t < kTileCount; ++t) {
     const Shape& s = shapes[t];
     if (N % s.tn != 0) continue;
-    const int64_t wgs = (int64_t)((M + s.tm - 1) / s.tm) * (N / s.tn);
+    const int64_t wgs = (int64_t)((M + s.tm - 1) / s.tm) * (N / s.tn) * S;
     const int64_t round = (int64_t)num_cus * s.per_cu, rem = wgs % round;
     auto one = [&](int n) {  // a round with n workgroups per CU
       const double latency = 0.4 / s.steps;
       const double loads = n * (s.tm + s.tn) * 64e-3 / 65.;
       const double mfma = (double)n * s.tm * s.tn / (64e3 * 1.47);
       const double step = latency > loads ? latency : loads;
-      return K / 32 * (step > mfma ? step : mfma) + 2.7 * n;
+      return K / S / 32 * (step > mfma ? step : mfma) + 2.7 * n;
     };
     double us = (double)(wgs / round) * one(s.per_cu);
     if (rem != 0) us += one(rem <= num_cus ? 1 : s.per_cu);
@@ -72,13 +72,13 @@ hipError_t launch_prefill_swiglu_bf16(const uint16_t* A, const uint16_t* W_gate_
   // tile is a whole number of unrolled rounds.
   using T = prefill::T256x192;
   const int tiles_m = (M + T::TM - 1) / T::TM;
-  if (prefill::choose_tile(M, 2 * F, K, num_cus) == prefill::k256x192 && num_cus == 256 &&
+  if (prefill::choose_tile(M, 2 * F, K, 1, num_cus) == prefill::k256x192 && num_cus == 256 &&
       32 % tiles_m == 0 && (K / 32) % T::ROUND == 0 && 2 * F % T::TN == 0) {
     COCO_LAUNCH((prefill::gemm_prefill_swiglu_persistent_kernel<T>), dim3(256), dim3(T::NT), 0, st,
                 (const bf16_t*)A, (const bf16_t*)W_gate_up, M, F, K, (bf16_t*)H, ss_in, eps);
     return hipGetLastError();
   }
-  return prefill::launch_mode<prefill::kSwiglu>(A, W_gate_up, M, 2 * F, K, ea, num_cus, st);
+  return prefill::launch_mode<prefill::kSwiglu>(A, W_gate_up, M, 2 * F, K, 1, ea, num_cus, st);
 }
 
 hipError_t launch_prefill_swiglu_plain_bf16(const uint16_t* A, const uint16_t* W_gate_up,
@@ -89,7 +89,7 @@ hipError_t launch_prefill_swiglu_plain_bf16(const uint16_t* A, const uint16_t* W
   PrefillEpiArgs ea{};
   ea.h = H;
   ea.h_rows = !h_tiled;
-  return prefill::launch_mode<prefill::kSwigluPlain>(A, W_gate_up, M, 2 * F, K, ea, num_cus, st);
+  return prefill::launch_mode<prefill::kSwigluPlain>(A, W_gate_up, M, 2 * F, K, 1, ea, num_cus, st);
 }
 
 }  // namespace coco

@@ -41,6 +41,14 @@ hipError_t launch_gather_rmsnorm_bf16(const uint16_t* src, const int32_t* row_id
                                       const uint16_t* gamma, float eps, uint16_t* h_out,
                                       const RowSlotArgs& rs, hipStream_t st);
 
+// Decode batches whose QKV projection runs on the tile kernel: h_out[i] =
+// bf16(x * gamma) of row src[row_idx ? row_idx[i] : i] in tile order, and
+// ss[s][i] = the row's sum of squares over K-slice s, with the bits of
+// launch_gemm_skinny_norm_bf16.
+hipError_t launch_gather_scale_bf16(const uint16_t* src, const int32_t* row_idx, int M, int d,
+                                    const uint16_t* gamma, uint16_t* h_out, float* ss, int S,
+                                    hipStream_t st);
+
 // RoPE table rope[p][j] = (cos, sin)(p * inv_freq[j]) for p < n_pos and
 // j < half, angle and both functions in fp64 (as the QKV epilogue computes
 // them), stored as fp32 pairs.
@@ -130,17 +138,12 @@ hipError_t launch_gemm_skinny_norm_bf16(const uint16_t* X, const int32_t* row_id
 hipError_t launch_gemm_skinny_swiglu_bf16(const uint16_t* A, const uint16_t* W_gate_up,
                                           uint16_t* H, int M, int F, int K, SkinnyPlan plan,
                                           bool h_tiled, hipStream_t st);
-// Whether the decode GEMM of (N, K) at M rows (fuse: the SwiGLU variant) runs
-// the row-split kernel, which reads its activations A in tile order
-// (tile_off); the other decode kernels read A row-major.
-bool skinny_reads_tiled(int N, int K, int M, bool fuse);
-
 // Prefill GEMMs (bf16, any M): A in tile order (tile_off; its buffer holds M
 // rounded up to 16 rows), W in tile order, N and K multiples of 128, unsplit
 // along K. The tile shape is chosen by (M, N, K) and the number of CUs and
 // changes no result. Epilogue inputs of the variants (unused fields zero):
 struct PrefillEpiArgs {
-  // residual variant (O projection)
+  // residual variant (O projection; x1: also the partial variant's output)
   const uint16_t* res_x = nullptr;   // residual rows [*][N] (bf16)
   const int32_t* res_idx = nullptr;  // row m's residual row (null: m)
   const uint16_t* gamma = nullptr;   // RMSNorm_2 gains [N]
@@ -186,6 +189,11 @@ hipError_t launch_prefill_swiglu_bf16(const uint16_t* A, const uint16_t* W_gate_
 hipError_t launch_prefill_swiglu_plain_bf16(const uint16_t* A, const uint16_t* W_gate_up,
                                             uint16_t* H, int M, int F, int K, bool h_tiled,
                                             int num_cus, hipStream_t st);
+// Decode projections of large batches: part[s][m][n] = sum over K-slice s (of
+// S) of A[m][k] * W[n][k], A in tile order; the same chain of MFMAs, and bits,
+// as launch_gemm_skinny_bf16 with that S (K a multiple of 128 S).
+hipError_t launch_tile_partial_bf16(const uint16_t* A, const uint16_t* W, float* part, int M,
+                                    int N, int K, int S, int num_cus, hipStream_t st);
 // QKV projection with RoPE and the cache append in its epilogue (head_dim
 // 128): queries to q_out [M][Hq*128] in bf16, keys (rotated) and values into
 // the paged cache tiles.
