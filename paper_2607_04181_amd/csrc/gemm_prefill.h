@@ -96,7 +96,7 @@ struct Tile {
   // with the 32-k step) are then known at compile time.
   static constexpr int ROUND = (SLOTS * KS) % 2 ? 2 * SLOTS : SLOTS;
   static_assert(TM % (16 * WM) == 0 && TN % (16 * WN) == 0 && TN % 32 == 0, "tile shape");
-  static_assert(SLOTS >= 3 && SLOTS <= 8 && SLOTS > RB, "ring slots");
+  static_assert(SLOTS >= 3 && SLOTS <= 8 && SLOTS > RB && RB <= 5, "ring slots");
   static_assert(LOADS * (AHEAD - 1) < 64, "vmcnt range");
 };
 
@@ -384,7 +384,9 @@ __global__ __launch_bounds__(T::NT) void gemm_prefill_kernel(const bf16_t* __res
   auto st_row = [&](int rq) -> float* {  // row rq of the staged group
     if constexpr (RB == 1) return (float*)s0 + rq * TNP;
     const int g = rq >> 4;
-    return (float*)(g == 0 ? s0 : g == 1 ? s1 : g == 2 ? s2 : s3) + (rq & 15) * TNP;
+    float* const hi = (float*)(RB > 4 && g > 3 ? s4 : s3);
+    return (g == 0 ? (float*)s0 : g == 1 ? (float*)s1 : g == 2 ? (float*)s2 : hi) +
+           (rq & 15) * TNP;
   };
   // Accumulator layout: lane (j4, c16) of block (i, j) holds rows
   // 16 (RB wm + i) + 4 j4 + r, r < 4, of column 16 (CB wn + j) + c16.
@@ -856,6 +858,8 @@ using T256x224 = Tile<256, 224, 4, 2, 1, 5>;
 using T256x192 = Tile<256, 192, 4, 2, 1, 5>;
 using T256x160 = Tile<256, 160, 4, 2, 1, 6>;
 using T256x128 = Tile<256, 128, 4, 2, 1, 6>;
+using T192x256 = Tile<192, 256, 4, 2, 1, 5>;
+using T160x256 = Tile<160, 256, 2, 4, 1, 6>;
 using T128x256 = Tile<128, 256, 4, 2, 1, 6>;
 using T128x160 = Tile<128, 160, 4, 2, 1, 6>;
 using T128x128 = Tile<128, 128, 4, 2, 2, 4>;
@@ -866,8 +870,8 @@ using T64x64 = Tile<64, 64, 2, 2, 2, 8>;
 using T64x32 = Tile<64, 32, 4, 1, 4, 6>;
 using T32x32 = Tile<32, 32, 2, 2, 4, 8>;
 enum TileId {
-  k256x224, k256x192, k256x160, k256x128, k128x256, k128x160, k128x128, k128x64, k64x160,
-  k64x128, k64x64, k64x32, k32x32, kTileCount
+  k256x224, k256x192, k256x160, k256x128, k192x256, k160x256, k128x256, k128x160, k128x128,
+  k128x64, k64x160, k64x128, k64x64, k64x32, k32x32, kTileCount
 };
 // The shape for an [M] x [N] x [K] product, run as S products of K / S; -1 if
 // none divides N.
@@ -892,6 +896,8 @@ hipError_t launch_mode(const uint16_t* A, const uint16_t* W, int M, int N, int K
     case k256x192: return launch_one<T256x192, MODE>(A, W, M, N, K, S, ea, st);
     case k256x160: return launch_one<T256x160, MODE>(A, W, M, N, K, S, ea, st);
     case k256x128: return launch_one<T256x128, MODE>(A, W, M, N, K, S, ea, st);
+    case k192x256: return launch_one<T192x256, MODE>(A, W, M, N, K, S, ea, st);
+    case k160x256: return launch_one<T160x256, MODE>(A, W, M, N, K, S, ea, st);
     case k128x256: return launch_one<T128x256, MODE>(A, W, M, N, K, S, ea, st);
     case k128x160: return launch_one<T128x160, MODE>(A, W, M, N, K, S, ea, st);
     case k128x128: return launch_one<T128x128, MODE>(A, W, M, N, K, S, ea, st);

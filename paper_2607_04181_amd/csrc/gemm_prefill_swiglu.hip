@@ -14,10 +14,13 @@ namespace prefill {
 //     loads-only ablation of the 256-row tiles runs at 54-60);
 //   * its MFMAs, n TM TN / 64 cycles at an effective 1.47 GHz (the clock under
 //     load times the MFMA pipe's share of a stage).
-// The five constants are a least-squares fit to 2,100 timed launches (13
-// shapes x 15 row counts from 1 to 2,048 x the four projections of the 8B, 32B
-// and 70B layers): 13% rms off the times, and the shape it picks takes on
-// average 0.1%, at worst 6% longer than the best one. Against one 256-row
+// The five constants are a least-squares fit to 2,100 timed launches (the 13
+// shapes other than 192 x 256 and 160 x 256, x 15 row counts from 1 to 2,048 x
+// the four projections of the 8B, 32B and 70B layers): 13% rms off the times,
+// and the shape it picks takes on average 0.1%, at worst 6% longer than the
+// best one. The two fill the gap between 128 and 256 rows, best of the others
+// against them (us): 8B gate/up 300 rows 92 -> 80, 380 rows 97 -> 90, 760 rows
+// 175 -> 162; 70B gate/up 160 rows 199 -> 183, 380 rows 364 -> 339. Against one 256-row
 // shape for every M: 8B, 300 rows: QKV 69 -> 30 us, O 43 -> 24, down 124 ->
 // 70; 32B, 512 rows, down 379 -> 212; 70B, 1,000 rows, O 187 -> 113 (256 x 256
 // tiles before).
@@ -28,10 +31,10 @@ int choose_tile(int M, int N, int K, int S, int num_cus) {
 #define COCO_SHAPE(T, per_cu) {T::TM, T::TN, T::AHEAD * T::KS, per_cu}
   static constexpr Shape shapes[kTileCount] = {
       COCO_SHAPE(T256x224, 1), COCO_SHAPE(T256x192, 1), COCO_SHAPE(T256x160, 1),
-      COCO_SHAPE(T256x128, 1), COCO_SHAPE(T128x256, 1), COCO_SHAPE(T128x160, 1),
-      COCO_SHAPE(T128x128, 1), COCO_SHAPE(T128x64, 1),  COCO_SHAPE(T64x160, 1),
-      COCO_SHAPE(T64x128, 2),  COCO_SHAPE(T64x64, 1),   COCO_SHAPE(T64x32, 1),
-      COCO_SHAPE(T32x32, 1)};
+      COCO_SHAPE(T256x128, 1), COCO_SHAPE(T192x256, 1), COCO_SHAPE(T160x256, 1),
+      COCO_SHAPE(T128x256, 1), COCO_SHAPE(T128x160, 1), COCO_SHAPE(T128x128, 1),
+      COCO_SHAPE(T128x64, 1),  COCO_SHAPE(T64x160, 1),  COCO_SHAPE(T64x128, 2),
+      COCO_SHAPE(T64x64, 1),   COCO_SHAPE(T64x32, 1),   COCO_SHAPE(T32x32, 1)};
 #undef COCO_SHAPE
   int best = -1;
   double best_us = 0.;

@@ -1,4 +1,4 @@
-"""The prefill GEMMs run on one of thirteen tile shapes, chosen by the call's
+"""The prefill GEMMs run on one of fifteen tile shapes, chosen by the call's
 rows: whole batches and their request-aligned shares below take different
 shapes for the same rows, and must give the same bits."""
 import pytest
@@ -11,23 +11,29 @@ from workloads import device as WD
 
 pytestmark = pytest.mark.gpu
 
-# (d, query heads, F), lengths, shares, request checked against the oracle.
+# (d, query heads, kv heads, F), lengths, shares, request checked against the oracle.
 # d = 2560, F = 4480: gate/up of 2100 rows on 256 x 160 tiles, 1500 on
 # 256 x 224, 1025 on 128 x 160, 513 on 256 x 128, 200 on 64 x 160, 87 on
 # 128 x 64; O and down from 256 x 128 to 32 x 32; QKV from 128 x 64 to 32 x 32.
-# d = 1792, F = 3584: gate/up of 1025 rows on 128 x 256 tiles. Lengths leave
-# partial row tiles and rows of several requests in one tile.
+# d = 1792, F = 3584: gate/up of 1025 rows on 128 x 256 tiles. 192- and 160-row
+# tiles: gate/up of 381 and 302 rows (F = 14336), O and down of 1340 and 1050
+# rows (d = 8192), QKV of 1050 rows (64 + 16 heads) and of 1290 (40 + 8).
+# Lengths leave partial row tiles and rows of several requests in one tile.
 CASES = [
-    ((2560, 5, 4480), [1500, 513, 33, 54], ([0], [1], [3, 2]), 2),
-    ((2560, 5, 4480), [825, 130, 70], ([0], [1, 2]), 2),
-    ((1792, 14, 3584), [765, 259, 1], ([2, 1], [0]), 2),
+    ((2560, 5, 1, 4480), [1500, 513, 33, 54], ([0], [1], [3, 2]), 2),
+    ((2560, 5, 1, 4480), [825, 130, 70], ([0], [1, 2]), 2),
+    ((1792, 14, 1, 3584), [765, 259, 1], ([2, 1], [0]), 2),
+    ((512, 4, 1, 14336), [250, 52, 79], ([0, 1], [2]), 1),
+    ((8192, 4, 1, 512), [1050, 250, 40], ([0], [1, 2]), 2),
+    ((512, 64, 8, 384), [1000, 50], ([0], [1]), 1),
+    ((1024, 40, 4, 384), [1250, 40], ([0], [1]), 1),
 ]
 
 
 @pytest.mark.parametrize("dims,lens,shares,req", CASES)
 def test_prefill_tile_shapes_agree_bit_exactly_and_match_oracle(dims, lens, shares, req):
-    d, hq, ffn = dims
-    shape = small_bf16_shape(d=d, hq=hq, hkv=1, ffn=ffn)
+    d, hq, hkv, ffn = dims
+    shape = small_bf16_shape(d=d, hq=hq, hkv=hkv, ffn=ffn)
     priors = [(37 * s) % 90 for s in range(len(lens))]
     b = ragged_prefill_batch(41, priors=priors, lens=lens, max_ctx=1600,
                              hidden_rows=sum(lens) + 7)
