@@ -339,10 +339,10 @@ __global__ __launch_bounds__(HD) void attn_combine_kernel(const float* __restric
 }
 
 // ---------------------------------------------------------------- prefill
-// Workgroup = (sequence, 128-row query tile, query head). Workgroups are
+// Workgroup = (sequence, 128- or 64-row query tile, query head). Workgroups are
 // remapped so that the query heads of one tile run back to back on one XCD
 // (blockIdx % 8) and share its L2 for the key/value tiles of their group.
-// Its sixteen waves form two key sets of eight; in each set a wave takes 16
+// Its waves form two key sets of eight (four); in each set a wave takes 16
 // rows of the tile as one 16-column tile. The key/value tiles are staged
 // through LDS eight blocks (128 keys) at a time by direct global->LDS loads
 // (each wave fetches one block's K or V tile as four contiguous 1 KB
@@ -359,8 +359,9 @@ __global__ __launch_bounds__(HD) void attn_combine_kernel(const float* __restric
 // of a long sequence's chunk see the most keys) against two workgroups of
 // eight waves per CU that each walk all the keys: 114-117 -> 100-102 us on
 // the 32B 2048-token chunked prefill (A/B, same box).
-constexpr int kPfRows = 128;  // query rows per workgroup
-constexpr int kPfLaunchWaves = 8;  // waves per key set, one 16-row column tile each (measured faster than 4 x 2)
+// Waves per key set, one 16-row column tile each (measured faster than 4 waves
+// of two).
+constexpr int kPfWaves = 8, kPfWavesFew = 4;
 constexpr int kPfKeySets = 2;      // key sets per workgroup
 constexpr int kPfBlk = 4;     // key blocks per stage
 // The running max of a row is kept while a stage's max stays within this
@@ -378,18 +379,19 @@ typedef __attribute__((address_space(3))) const volatile u32x2_t lds_u32x2_cv;
 // register moves to split.
 __device__ __forceinline__ u32x2_t lds_read8(const bf16_t* p) { return *(lds_u32x2_cv*)p; }
 
-// WAVES waves of COLS 16-column tiles each cover the workgroup's 128 rows;
+// WAVES waves of COLS 16-column tiles each cover the workgroup's rows;
 // KS sets of WAVES waves split every stage's keys between them (set kh takes
 // blocks kh * kPfBlk .. of a stage of KS * kPfBlk blocks) and merge their
 // softmax states in LDS at the end.
 template <int WAVES, int COLS, int KS>
-__global__ __launch_bounds__(WAVES * KS * 64, KS > 1 ? 1 : 8 / WAVES) void attn_prefill_kernel(
+__global__ __launch_bounds__(WAVES * KS * 64) void attn_prefill_kernel(
     const bf16_t* __restrict__ q, const bf16_t* __restrict__ k_cache,
     const bf16_t* __restrict__ v_cache, const int32_t* __restrict__ block_table, int max_blocks,
     const int32_t* __restrict__ ctx_lens, const int32_t* __restrict__ positions,
     const int32_t* __restrict__ seq_starts, int n_seqs, int Hq, int Hkv, float scale_log2,
     bf16_t* __restrict__ o) {
   static_assert(KS == 1 || KS == 2, "one or two key sets");
+  constexpr int kPfRows = WAVES * COLS * 16;  // query rows per workgroup
   constexpr int kStBlk = kPfBlk * KS;  // key blocks per stage
   // Two K and two V slots of a stage's kStBlk tiles each, in one LDS array.
   constexpr int kSlot = kStBlk * kTileElems;
@@ -455,7 +457,8 @@ __global__ __launch_bounds__(WAVES * KS * 64, KS > 1 ? 1 : 8 / WAVES) void attn_
 
   // The stage's blocks (clamped to the last block: a repeat that the causal
   // mask hides) x {K, V} tiles, four 1 KB pieces each; wave wv stages tiles
-  // wv, wv + WAVES * KS, ... into LDS.
+  // wv, wv + WAVES * KS, ... into LDS. (Block-table lookups one stage ahead
+  // measured slower: 8B, 300 rows over up to 2,049 cached tokens 33 -> 40 us.)
   auto issue = [&](int st) {
 #pragma unroll
     for (int tt = wv; tt < 2 * kStBlk; tt += WAVES * KS) {
@@ -725,17 +728,32 @@ hipError_t launch_attn_prefill_bf16(const uint16_t* q, const uint16_t* k_cache,
                                     int max_blocks, const int32_t* ctx_lens,
                                     const int32_t* positions, const int32_t* seq_starts,
                                     int n_seqs, int n_rows, int Hq, int Hkv, uint16_t* o,
-                                    hipStream_t st) {
+                                    int num_cus, hipStream_t st) {
   if (n_rows <= 0) return hipSuccess;
   const float scale_log2 = kLog2e / sqrtf((float)HD);
-  // Upper bound on the per-sequence 128-row tiles; workgroups past the last
-  // tile return at once.
-  const int64_t tiles = (n_rows + kPfRows - 1) / kPfRows + n_seqs;
+  // 64-row tiles, with the same bits, halve a workgroup's work and double the
+  // workgroups: for calls whose rows give them about one per CU at most (a CU
+  // holds one, by its LDS), of sequences that on average fill more than half
+  // of a 128-row tile (shorter ones leave the waves of the second half idle).
+  // 128 / 64 rows, us: 8B, 300 rows over up to 2,049 cached tokens 40.3 / 32.8,
+  // 150 rows over 1,500 30.7 / 26.1; past a round, 500 rows 20.1 / 23.9; short
+  // sequences, 40 rows of three on the 70B layer 17.7 / 18.3.
+  const bool few = n_rows > 64 * (int64_t)n_seqs &&
+                   ((n_rows + 63) / 64 + n_seqs / 2) * (int64_t)Hq <= num_cus;
+  // Upper bound on the per-sequence tiles; workgroups past the last tile
+  // return at once.
+  const int rows = 16 * (few ? kPfWavesFew : kPfWaves);
+  const int64_t tiles = (n_rows + rows - 1) / rows + n_seqs;
   if (tiles * Hq > 0x7fffffff) return hipErrorInvalidValue;
-  COCO_LAUNCH((attn_prefill_kernel<kPfLaunchWaves, 8 / kPfLaunchWaves, kPfKeySets>),
-                     dim3((unsigned)(tiles * Hq)), dim3(kPfLaunchWaves * kPfKeySets * 64), 0, st, q,
-                     k_cache, v_cache, block_table, max_blocks, ctx_lens, positions, seq_starts,
-                     n_seqs, Hq, Hkv, scale_log2, o);
+  const dim3 grid((unsigned)(tiles * Hq));
+  if (few)
+    COCO_LAUNCH((attn_prefill_kernel<kPfWavesFew, 1, kPfKeySets>), grid,
+                dim3(kPfWavesFew * kPfKeySets * 64), 0, st, q, k_cache, v_cache, block_table,
+                max_blocks, ctx_lens, positions, seq_starts, n_seqs, Hq, Hkv, scale_log2, o);
+  else
+    COCO_LAUNCH((attn_prefill_kernel<kPfWaves, 1, kPfKeySets>), grid,
+                dim3(kPfWaves * kPfKeySets * 64), 0, st, q, k_cache, v_cache, block_table,
+                max_blocks, ctx_lens, positions, seq_starts, n_seqs, Hq, Hkv, scale_log2, o);
   return hipGetLastError();
 }
 

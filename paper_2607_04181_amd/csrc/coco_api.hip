@@ -693,7 +693,7 @@ int attention(coco_layer* H, const Work& W, const coco_layer_weights& w, int M,
     HIPCHK(launch_attn_prefill_bf16((const bf16_t*)W.q, (const bf16_t*)w.k_cache,
                                     (const bf16_t*)w.v_cache, bt, c.max_blocks_per_seq, ctx,
                                     positions, seq_starts, n_seqs, M, c.n_q_heads, c.n_kv_heads,
-                                    (bf16_t*)W.o, st));
+                                    (bf16_t*)W.o, H->num_cus, st));
   }
   return COCO_OK;
 }

@@ -271,7 +271,7 @@ hipError_t launch_attn_prefill_bf16(const uint16_t* q, const uint16_t* k_cache,
                                     int max_blocks, const int32_t* ctx_lens,
                                     const int32_t* positions, const int32_t* seq_starts,
                                     int n_seqs, int n_rows, int Hq, int Hkv, uint16_t* o,
-                                    hipStream_t st);
+                                    int num_cus, hipStream_t st);
 
 // fp32 path, decode and prefill alike (hd a multiple of 32, at most 256).
 hipError_t launch_attn_f32(const float* q, const float* k_cache, const float* v_cache,
