@@ -93,11 +93,10 @@ def test_c2_llama8b_decode_batch64_sampled_rows():
 
 
 def test_llama8b_decode_300_rows_matches_oracle_and_splits():
-    """300 decode rows of the 8B layer: the gate/up and down projections
-    (7- and 8-wave plans) take the row-split GEMM in two passes (256 rows,
-    then 44), QKV and O three 128-row passes. Sampled rows of both passes
-    against the oracle; the whole batch bit-identical to a 200/100 split
-    (one row-split pass, then the 128-row kernel)."""
+    """300 decode rows of the 8B layer: above 128 rows every projection takes
+    the tile GEMM. Sampled rows against the oracle; the whole batch
+    bit-identical to a 200/100 split (the 100 rows' QKV and gate/up on the
+    128-row weight-streaming kernel)."""
     wl = W.c2_llama8b_decode(300)
     b, shape = wl.batch, wl.shape
     rep = Replica.for_batch(shape, wl.tag, 1, b)
@@ -124,10 +123,9 @@ def test_llama8b_decode_300_rows_matches_oracle_and_splits():
 
 def test_llama8b_decode_129_rows_across_gemm_row_limits():
     """129 decode rows of the 8B layer split at the decode GEMMs' row limits:
-    the whole batch (gate/up and down: one 256-row pass of the row-split
-    GEMM, mostly past M), 65 rows (down: a 128-row pass of it), 64 rows
-    (the 64-row kernel) give identical bits; sampled rows against the
-    oracle."""
+    the whole batch (every projection on the tile GEMM), 65 rows (QKV and
+    gate/up on the 128-row weight-streaming kernel), 64 rows (on the 64-row
+    one) give identical bits; sampled rows against the oracle."""
     wl = W.c2_llama8b_decode(129)
     b, shape = wl.batch, wl.shape
     rep = Replica.for_batch(shape, wl.tag, 1, b)
@@ -153,10 +151,9 @@ def test_llama8b_decode_129_rows_across_gemm_row_limits():
 
 
 def test_qwen32b_decode_192_rows_row_split_gate_up():
-    """192 decode rows of the 32B layer: its 8-wave gate/up plan takes the
-    row-split GEMM's 256-row pass with the SwiGLU epilogue; two 96-row
-    halves (its 128-row pass) give identical bits, and sampled rows match
-    the oracle."""
+    """192 decode rows of the 32B layer: every projection takes the tile
+    GEMM; two 96-row halves (QKV, O and down on the weight-streaming kernel)
+    give identical bits, and sampled rows match the oracle."""
     shape = W.QWEN32B
     rng = np.random.default_rng(192)
     prior = np.clip(np.exp(rng.normal(np.log(1024), 0.8, 192)).astype(np.int64), 16, 4096)
@@ -279,7 +276,7 @@ def test_c4_qwen32b_prefill_then_decode():
     kv_dec = _kv_new_tokens(lay, dec, range(dec.n_seqs))
     dsnap.restore()
     # Two 64-row halves (the 64-row GEMM kernels) give the bits of the whole
-    # batch (the 8-wave gate/up plan's 128-row pass of the row-split kernel).
+    # batch (128-row ones; gate/up on the tile GEMM).
     halves = WD.hidden_tensor(shape, wl.tag + "dec", dec.hidden_rows)
     for part in (np.arange(0, 64), np.arange(64, 128)):
         rep.forward(0, halves, WD.batch_tensors(dec.select(part)))

@@ -271,12 +271,9 @@ def test_prefill_request_aligned_split_is_bit_identical():
         assert np.array_equal(k1, k2) and np.array_equal(v1, v2)
 
 
-# Gate/up plans at d = 640, F = 3456 (36 column tiles of 96 outputs): (priors,
-# lengths, request-aligned shares, request checked against the oracle). The
-# whole batch takes the persistent kernel (row tiles dividing 32): 2048 rows
-# (8 row tiles, up to two column tiles per workgroup) and 4096 rows (16 row
-# tiles, up to three); the shares of 900 rows (persistent, one tile each),
-# 1148, 1500 and 2596 rows (5, 6 and 11 row tiles) take the one-tile kernel.
+# Gate/up at d = 640, F = 3456: (priors, lengths, request-aligned shares, request
+# checked against the oracle). Tile shapes: 2048 and 900 rows 256 x 128, 1148
+# 128 x 256, 4096 and 2596 160 x 256, 1500 256 x 192.
 GATE_UP_PLANS = [
     ([0, 100, 37], [900, 248, 900], ([0], [1, 2]), 1),
     ([0, 64, 5], [1500, 300, 2296], ([0], [1, 2]), 1),
@@ -285,11 +282,9 @@ GATE_UP_PLANS = [
 
 @pytest.mark.parametrize("priors,lens,shares,req", GATE_UP_PLANS)
 def test_prefill_gate_up_plans_agree_bit_exactly_and_match_oracle(priors, lens, shares, req):
-    """The persistent gate/up GEMM, where a workgroup takes its row tile
-    through several column tiles with the load ring running across them,
-    against request-aligned shares on the one-tile kernel: rows and appended
-    cache bytes bit-identical; a request's rows and cache against the
-    oracle."""
+    """Large gate/up products against request-aligned shares on other tile
+    shapes: rows and appended cache bytes bit-identical; a request's rows and
+    cache against the oracle."""
     shape = small_bf16_shape(d=640, hq=5, hkv=1, ffn=3456)
     b = ragged_prefill_batch(31, priors=priors, lens=lens, max_ctx=2560,
                              hidden_rows=sum(lens) + 52)
@@ -319,9 +314,8 @@ def test_prefill_gate_up_plans_agree_bit_exactly_and_match_oracle(priors, lens, 
 
 
 def test_prefill_gate_up_single_row_tile_matches_oracle():
-    """One request of 200 rows at d = 640, F = 3456: a single row tile, so the
-    persistent gate/up GEMM gives each of 36 workgroups one column tile and
-    the other 220 leave at once."""
+    """One request of 200 rows at d = 640, F = 3456: a partial row tile of the
+    gate/up GEMM, a fraction of the chip's workgroups."""
     shape = small_bf16_shape(d=640, hq=5, hkv=1, ffn=3456)
     b = ragged_prefill_batch(32, priors=[40], lens=[200], max_ctx=256, hidden_rows=230)
     rep = Replica.for_batch(shape, "s32", 1, b)
@@ -428,10 +422,7 @@ def test_prefill_span_equals_successive_layers_bit_exactly():
 @pytest.mark.parametrize("hq", [5, 3])
 def test_prefill_with_an_odd_head_count_matches_oracle(hq):
     """One KV head with five (three) query heads and d = 384: the QKV width
-    of 7 (5) heads takes the narrow-tile QKV GEMM with 224-column (160-column)
-    tiles of whole rotation pairs, split unevenly between the two waves of a
-    row quarter, and d takes the narrow O and down GEMMs with three
-    128-column tiles."""
+    of 7 (5) heads is tiled by whole rotation pairs that cross heads."""
     shape = small_bf16_shape(d=384, hq=hq, hkv=1, ffn=768)
     b = ragged_prefill_batch(13, priors=[0, 50, 17], lens=[30, 70, 16], max_ctx=256,
                              hidden_rows=150)
