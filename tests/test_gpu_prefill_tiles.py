@@ -18,9 +18,9 @@ pytestmark = pytest.mark.gpu
 # d = 1792, F = 3584: gate/up of 1025 rows on 128 x 256 tiles. 192- and 160-row
 # tiles: gate/up of 381 and 302 rows (F = 14336), O and down of 1340 and 1050
 # rows (d = 8192), QKV of 1050 rows (64 + 16 heads) and of 1290 (40 + 8).
-# d = 640, F = 5184: gate/up of 2048 and 4096 rows on the persistent 256 x 192
+# d = 640, F = 5760: gate/up of 2048 and 4096 rows on the persistent 256 x 192
 # kernel (8 and 16 row tiles, up to two and four column tiles per workgroup),
-# 2296 rows (9 row tiles) on the one-tile 256 x 192 one.
+# the shares of 1500 and 2296 rows on 256 x 160.
 # Lengths leave partial row tiles and rows of several requests in one tile.
 CASES = [
     ((2560, 5, 1, 4480), [1500, 513, 33, 54], ([0], [1], [3, 2]), 2),
@@ -30,8 +30,8 @@ CASES = [
     ((8192, 4, 1, 512), [1050, 250, 40], ([0], [1, 2]), 2),
     ((512, 64, 8, 384), [1000, 50], ([0], [1]), 1),
     ((1024, 40, 4, 384), [1250, 40], ([0], [1]), 1),
-    ((640, 5, 1, 5184), [1500, 300, 248], ([0], [2, 1]), 1),
-    ((640, 5, 1, 5184), [1500, 300, 1000, 1296], ([0], [1], [3, 2]), 1),
+    ((640, 5, 1, 5760), [1500, 300, 248], ([0], [2, 1]), 1),
+    ((640, 5, 1, 5760), [1500, 300, 1000, 1296], ([0], [1], [3, 2]), 1),
 ]
 
 
