@@ -91,6 +91,17 @@ __device__ __forceinline__ void stage_barrier() {
   __atomic_signal_fence(__ATOMIC_SEQ_CST);
 }
 
+// Between LDS stores and loads by which the lanes of one wave pass values to
+// each other without a barrier. The hardware performs a wave's LDS operations
+// in order; the compiler, which sees one lane's addresses, may swap a store
+// and a load that differ in that lane but meet in another. No LDS operation
+// moves across this point; it costs no instruction.
+__device__ __forceinline__ void wave_lds_order() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront", "local");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront", "local");
+}
+
 __device__ __forceinline__ float wave_sum(float v) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, kWave);

@@ -632,8 +632,7 @@ __global__ __launch_bounds__(T::NT) void gemm_prefill_kernel(const bf16_t* __res
         mine[row2 * kWO + 8 * j + (c16 & 7)] = (bf16_t)f32_to_bf16(y[0]);
         mine[(row2 + 1) * kWO + 8 * j + (c16 & 7)] = (bf16_t)f32_to_bf16(y[1]);
       }
-      // Reads of the rows just written by this wave (LDS operations of a
-      // wave are performed in order).
+      wave_lds_order();  // the rows just written, by this wave's other lanes
 #pragma unroll
       for (int c0 = 0; c0 < 16 * CB; c0 += 64) {
         const int row = (c0 + lane) & 15, pc = (c0 + lane) >> 4;
@@ -644,6 +643,7 @@ __global__ __launch_bounds__(T::NT) void gemm_prefill_kernel(const bf16_t* __res
           if (m < M) *(u32x4_t*)(ea.h + (rows ? (int64_t)m * F + o : tile_off(m, o, F))) = v;
         }
       }
+      wave_lds_order();  // read before the next block overwrites them
     }
   }
 }
@@ -832,8 +832,7 @@ __global__ __launch_bounds__(T::NT) void gemm_prefill_swiglu_persistent_kernel(
         mine[row2 * kWO + 8 * j + (c16 & 7)] = (bf16_t)f32_to_bf16(y[0]);
         mine[(row2 + 1) * kWO + 8 * j + (c16 & 7)] = (bf16_t)f32_to_bf16(y[1]);
       }
-      // Reads of the rows just written by this wave (LDS operations of a
-      // wave are performed in order).
+      wave_lds_order();  // the rows just written, by this wave's other lanes
       const int mr = m0 + rb;
       bf16_t* const hb = H + ((int64_t)(mr >> 4) * (F >> 5) + (o0 >> 5)) * 512;
 #pragma unroll
@@ -846,6 +845,7 @@ __global__ __launch_bounds__(T::NT) void gemm_prefill_swiglu_persistent_kernel(
             *(u32x4_t*)(hb + ((kk >> 5) * 512 + ((kk & 31) >> 3) * 128 + row * 8)) = v;
         }
       }
+      wave_lds_order();  // read before the next block overwrites them
     }
   }
   wait_vmcnt<0>();  // no direct load outlives the workgroup

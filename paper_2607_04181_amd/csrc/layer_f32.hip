@@ -178,7 +178,9 @@ __global__ __launch_bounds__(kFThreads) void layer_f32_gemm_kernel(const float* 
   for (int c = wv; c < chunks; c += kFWaves) {
     put(c);
     load(c + kFWaves);
+    wave_lds_order();  // other lanes' pieces
     mul();
+    wave_lds_order();  // read before the next chunk overwrites them
   }
 
   // The waves' sums, in wave order; a wave's worth of threads per row tile

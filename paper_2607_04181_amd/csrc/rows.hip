@@ -276,6 +276,7 @@ __global__ __launch_bounds__(kEpiHeads * kWave) void qkv_epilogue_kernel(
     // split_off[n_seqs + 2]. Dealt out in that order (snake-wise over the
     // workgroups), items of similar size meet at the end of the kernel.
     for (int r = lane; r < kDecodeSplit; r += kWave) wl_rank[r] = 0;
+    wave_lds_order();  // wl_rank is counted, read and moved by this wave alone
     int run = 0;
     if (lane == 0) split_off[0] = 0;
     for (int base = 0; base < n_seqs; base += kWave) {
@@ -293,6 +294,7 @@ __global__ __launch_bounds__(kEpiHeads * kWave) void qkv_epilogue_kernel(
       if (s < n_seqs) split_off[s + 1] = run + v;
       run += __shfl(v, kWave - 1, kWave);
     }
+    wave_lds_order();
     // Sizes largest first: wl_rank[r] becomes the number of partial
     // partitions longer than r keys (a suffix sum, four sizes per lane).
     static_assert(kDecodeSplit == 4 * kWave, "four partition sizes per lane");
@@ -315,6 +317,7 @@ __global__ __launch_bounds__(kEpiHeads * kWave) void qkv_epilogue_kernel(
       acc += c[e];
     }
     if (lane == kWave - 1) split_off[n_seqs + 1] = incl;
+    wave_lds_order();
     for (int base = 0; base < n_seqs; base += kWave) {
       const int s = base + lane;
       const int n = s < n_seqs ? max(0, min(ctx_lens[s], positions[s] + 1)) : 0;
