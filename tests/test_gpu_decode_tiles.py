@@ -11,10 +11,11 @@ from workloads import device as WD
 
 pytestmark = pytest.mark.gpu
 
-# d, query heads, F: 4096-wide shapes whose projections plan 4 and 8 waves in
-# one round with 4 and 8 K-slices (O 4096 x 4096, down 4096 x 4096), and a
-# narrow one with unsplit 4-wave plans of a few workgroups. Row counts on both
-# sides of 64 and 128, none a multiple of a tile.
+# d, query heads, F: a 4096-wide shape whose O and down projections (4096 x
+# 4096) plan 4 waves and gate/up (8192 x 4096) 8, each in one round with 4
+# K-slices, its QKV unsplit; and a narrow one with unsplit 4-wave plans of a few
+# workgroups. Row counts on both sides of 64 and 128, none a multiple of a tile.
+# (8 K-slices and a split QKV: test_tile_coverage.py.)
 CASES = [((4096, 32, 4096), 131, ([70], [61])), ((4096, 32, 4096), 97, ([65], [31], [1])),
          ((512, 8, 768), 201, ([128], [72], [1])), ((512, 8, 768), 129, ([65], [64]))]
 

@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 
 # (d, query heads, kv heads, F), lengths, shares, request checked against the oracle.
 # d = 2560, F = 4480: gate/up of 2100 rows on 256 x 160 tiles, 1500 on
-# 256 x 224, 1025 on 128 x 160, 513 on 256 x 128, 200 on 64 x 160, 87 on
+# 256 x 224, 1025 on 160 x 256, 513 on 256 x 128, 200 on 64 x 160, 87 on
 # 128 x 64; O and down from 256 x 128 to 32 x 32; QKV from 128 x 64 to 32 x 32.
 # d = 1792, F = 3584: gate/up of 1025 rows on 128 x 256 tiles. 192- and 160-row
 # tiles: gate/up of 381 and 302 rows (F = 14336), O and down of 1340 and 1050
