@@ -243,42 +243,27 @@ __global__ __launch_bounds__(T::NT) void gemm_prefill_kernel(const bf16_t* __res
       w[j] = __builtin_bit_cast(
           bf16x8_t, *(const u32x4_t*)(s + (AB + (wn * CB + j) * KS + ks) * 512 + lane * 8));
   };
-  auto mfma_step = [&](const bf16x8_t* a, const bf16x8_t* w, auto first) {
+  auto mfma_step = [&](const bf16x8_t* a, const bf16x8_t* w, auto loads) {
 #pragma unroll
     for (int i = 0; i < RB; ++i)
 #pragma unroll
       for (int j = 0; j < CB; ++j)
         acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[i], w[j], acc[i][j], 0, 0, 0);
-    // Large sub-tiles: the stage's direct loads after the first four MFMAs
-    // (the MFMA pipe restarts right after the barrier), then the fragment
-    // reads of the next step interleaved with these MFMAs.
+    // Large sub-tiles: in the step that issues a stage's direct loads, those
+    // after the first four MFMAs (the MFMA pipe restarts right after the
+    // barrier), then the fragment reads of the next step interleaved with these
+    // MFMAs.
     if constexpr (RB * CB >= 8 + RB + CB) {
-      // first: loads after this many MFMAs (0: none in this step)
-      constexpr int kFirst = decltype(first)::value;
-      constexpr int kRd = RB + CB;
-      if constexpr (kFirst == 0) {
-        for (int g = 0; g < kRd; ++g) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
-          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // DS read
-        }
-        __builtin_amdgcn_sched_group_barrier(0x008, RB * CB - kRd, 0);
-      } else if constexpr (kFirst < kRd) {
+      constexpr int kFirst = decltype(loads)::value ? 4 : 0;
+      if constexpr (kFirst != 0) {
         __builtin_amdgcn_sched_group_barrier(0x008, kFirst, 0);  // MFMA
         __builtin_amdgcn_sched_group_barrier(0x020, LOADS, 0);   // VMEM read
-        for (int g = 0; g < kRd; ++g) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
-          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // DS read
-        }
-        __builtin_amdgcn_sched_group_barrier(0x008, RB * CB - kFirst - kRd, 0);
-      } else {
-        for (int g = 0; g < kRd; ++g) {
-          __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
-          __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // DS read
-        }
-        __builtin_amdgcn_sched_group_barrier(0x008, kFirst - kRd, 0);  // MFMA
-        __builtin_amdgcn_sched_group_barrier(0x020, LOADS, 0);         // VMEM read
-        __builtin_amdgcn_sched_group_barrier(0x008, RB * CB - kFirst, 0);
       }
+      for (int g = 0; g < RB + CB; ++g) {
+        __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
+        __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);  // DS read
+      }
+      __builtin_amdgcn_sched_group_barrier(0x008, RB * CB - kFirst - RB - CB, 0);
     }
   };
 
@@ -313,7 +298,7 @@ __global__ __launch_bounds__(T::NT) void gemm_prefill_kernel(const bf16_t* __res
   // One unrolled round: stages st0 .. st0 + ROUND - 1. In the last, partial
   // round (masked) stages past the end load the last stage again and multiply
   // nothing.
-  auto ring_round = [&](int st0, auto masked, auto first) {
+  auto ring_round = [&](int st0, auto masked) {
 #pragma unroll
     for (int u = 0; u < ROUND; ++u) {
       const int st = st0 + u;
@@ -329,19 +314,19 @@ __global__ __launch_bounds__(T::NT) void gemm_prefill_kernel(const bf16_t* __res
           read_frags(ring[(u + 1) % SLOTS], 0, fa[cur ^ 1], fw[cur ^ 1]);
         if (!decltype(masked)::value || st < stages) {
           if (ks == 0)
-            mfma_step(fa[cur], fw[cur], first);
+            mfma_step(fa[cur], fw[cur], std::true_type{});
           else
-            mfma_step(fa[cur], fw[cur], std::integral_constant<int, 0>{});
+            mfma_step(fa[cur], fw[cur], std::false_type{});
         }
       }
     }
   };
   const int full_end = stages - stages % ROUND;
-  auto main_loop = [&](auto first) {
-    for (int st0 = 0; st0 < full_end; st0 += ROUND) ring_round(st0, std::false_type{}, first);
-    if (full_end < stages) ring_round(full_end, std::true_type{}, first);
+  auto main_loop = [&]() {
+    for (int st0 = 0; st0 < full_end; st0 += ROUND) ring_round(st0, std::false_type{});
+    if (full_end < stages) ring_round(full_end, std::true_type{});
   };
-  main_loop(std::integral_constant<int, 4>{});
+  main_loop();
   wait_vmcnt<0>();  // no direct load outlives the workgroup
 
   // Epilogues, in the idle ring. The residual, scatter and QKV epilogues
