@@ -778,19 +778,19 @@ int decode_layer(coco_layer* H, const Work& W, const coco_layer_weights& w, cons
   }
   // RoPE, local cache append.
   TIMED(COCO_K_QKV_EPILOGUE,
-        HIPCHK(launch_qkv_epilogue<bf16_t>(W.part, plan.S, M, Hq, Hkv, hd, positions, nullptr, M,
-                                           bt, c.max_blocks_per_seq, H->inv_freq, q,
-                                           (bf16_t*)w.k_cache, (bf16_t*)w.v_cache, ctx,
-                                           W.split_off, H->max_splits, W.ss, d, c.rms_eps, st)));
+        HIPCHK(launch_qkv_epilogue_bf16(W.part, plan.S, M, Hq, Hkv, hd, positions, bt,
+                                        c.max_blocks_per_seq, H->inv_freq, q,
+                                        (bf16_t*)w.k_cache, (bf16_t*)w.v_cache, ctx, W.split_off,
+                                        H->max_splits, W.ss, d, c.rms_eps, st)));
   // Attention over the paged cache.
   if ((rc = attention(H, W, w, M, positions, nullptr, M, bt, ctx, lay.o, st))) return rc;
   // O projection + residual + RMSNorm_2.
   TIMED(COCO_K_GEMM_O,
         if ((rc = gemm(H, W.part, o, (const bf16_t*)w.w_o, M, d, Hq * hd, &S, st))) return rc);
   TIMED(COCO_K_RESIDUAL_NORM,
-        HIPCHK(launch_residual_rmsnorm<bf16_t>(W.part, S, M, d, x_src, x_idx,
-                                               (const bf16_t*)w.gamma_mlp, c.rms_eps, W.x1, h2,
-                                               lay.h2, st)));
+        HIPCHK(launch_residual_rmsnorm_bf16(W.part, S, M, d, x_src, x_idx,
+                                            (const bf16_t*)w.gamma_mlp, c.rms_eps, W.x1, h2,
+                                            lay.h2, st)));
   // SwiGLU MLP: in the gate/up GEMM's epilogue whenever that GEMM is not split
   // along K.
   if (tile_swiglu(H, M)) {
@@ -804,13 +804,13 @@ int decode_layer(coco_layer* H, const Work& W, const coco_layer_weights& w, cons
   } else {
     TIMED(COCO_K_GEMM_GATE_UP,
           if ((rc = gemm(H, W.part, h2, (const bf16_t*)w.w_gate_up, M, 2 * F, d, &S, st))) return rc);
-    TIMED(COCO_K_SWIGLU, HIPCHK(launch_swiglu<bf16_t>(W.part, S, M, F, u, lay.u, st)));
+    TIMED(COCO_K_SWIGLU, HIPCHK(launch_swiglu_bf16(W.part, S, M, F, u, lay.u, st)));
   }
   // Down projection and residual.
   TIMED(COCO_K_GEMM_DOWN,
         if ((rc = gemm(H, W.part, u, (const bf16_t*)w.w_down, M, d, F, &S, st))) return rc);
   TIMED(COCO_K_RESIDUAL_SCATTER,
-        HIPCHK(launch_residual_scatter<bf16_t>(W.part, S, M, d, W.x1, y, y_idx, st)));
+        HIPCHK(launch_residual_scatter_bf16(W.part, S, M, d, W.x1, y, y_idx, st)));
   return COCO_OK;
 }
 

@@ -43,26 +43,10 @@ __device__ __forceinline__ float silu_mul(float g, float u) {
   return g * __builtin_amdgcn_rcpf(1.0f + e) * u;
 }
 
-// Element load/store for the two activation types.
-template <typename T> struct Elem;
-template <> struct Elem<bf16_t> {
-  static __device__ __forceinline__ float load(const bf16_t* p) { return bf16_to_f32(*p); }
-  static __device__ __forceinline__ void store(bf16_t* p, float v) { *p = (bf16_t)f32_to_bf16(v); }
-};
-template <> struct Elem<float> {
-  static __device__ __forceinline__ float load(const float* p) { return *p; }
-  static __device__ __forceinline__ void store(float* p, float v) { *p = v; }
-};
-
-// Four consecutive elements (p 8-byte aligned for bf16, 16-byte for fp32) in
-// one store.
+// Four consecutive elements (p 8-byte aligned) in one store.
 __device__ __forceinline__ void store4(bf16_t* p, float a, float b, float c, float d) {
   typedef uint32_t u2 __attribute__((ext_vector_type(2)));
   *(u2*)p = u2{pack_bf16x2(a, b), pack_bf16x2(c, d)};
-}
-__device__ __forceinline__ void store4(float* p, float a, float b, float c, float d) {
-  typedef float f4 __attribute__((ext_vector_type(4)));
-  *(f4*)p = f4{a, b, c, d};
 }
 
 // Waits until at most N vector-memory operations of this wave are in flight

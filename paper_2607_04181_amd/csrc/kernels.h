@@ -55,43 +55,39 @@ hipError_t launch_gather_scale_bf16(const uint16_t* src, const int32_t* row_idx,
 hipError_t launch_rope_table(const double* inv_freq, int half, int n_pos, float* rope,
                              hipStream_t st);
 
-// Sum of S split-K partials of the QKV projection, RoPE on query and key
-// heads, queries to q_out [M][Hq*hd], keys/values into the paged cache.
-// With ss non-null (decode, RMSNorm_1 folded into the projection), each row's
-// sums are first scaled by 1 / sqrt(sum_s ss[s][row] / d + eps).
-// With split_off non-null (decode), one workgroup also writes the decode
-// attention's work list (layout at launch_attn_decode_bf16) from the keys
-// each row attends, min(ctx_lens, positions + 1) (partition counts capped at
-// max_splits).
-template <typename T>
-hipError_t launch_qkv_epilogue(const float* part, int S, int M, int Hq, int Hkv, int hd,
-                               const int32_t* positions, const int32_t* seq_starts,
-                               int n_seqs, const int32_t* block_table, int max_blocks,
-                               const double* inv_freq, T* q_out, T* k_cache, T* v_cache,
-                               const int32_t* ctx_lens, int32_t* split_off, int max_splits,
-                               const float* ss, int d, float eps, hipStream_t st);
+// Decode: sum of S split-K partials of the QKV projection, each row's sums
+// scaled by 1 / sqrt(sum_s ss[s][row] / d + eps) (RMSNorm_1, folded into the
+// projection), RoPE on query and key heads, queries to q_out [M][Hq*hd],
+// keys/values into the paged cache. One workgroup also writes the decode
+// attention's work list split_off (layout at launch_attn_decode_bf16) from the
+// keys each row attends, min(ctx_lens, positions + 1) (partition counts capped
+// at max_splits).
+hipError_t launch_qkv_epilogue_bf16(const float* part, int S, int M, int Hq, int Hkv, int hd,
+                                    const int32_t* positions, const int32_t* block_table,
+                                    int max_blocks, const double* inv_freq, uint16_t* q_out,
+                                    uint16_t* k_cache, uint16_t* v_cache,
+                                    const int32_t* ctx_lens, int32_t* split_off, int max_splits,
+                                    const float* ss, int d, float eps, hipStream_t st);
 
 // x1 = x + sum_s part[s]  (fp32);  h2 = RMSNorm(x1) * gamma. Row i of x is
 // x[row_idx ? row_idx[i] : i]. tiled: h2 in tile order.
-template <typename T>
-hipError_t launch_residual_rmsnorm(const float* part, int S, int M, int d, const T* x,
-                                   const int32_t* row_idx, const T* gamma, float eps, float* x1,
-                                   T* h2, bool tiled, hipStream_t st);
+hipError_t launch_residual_rmsnorm_bf16(const float* part, int S, int M, int d,
+                                        const uint16_t* x, const int32_t* row_idx,
+                                        const uint16_t* gamma, float eps, float* x1,
+                                        uint16_t* h2, bool tiled, hipStream_t st);
 
 // u = silu(sum_s gate) * sum_s up, part rows [2F] in the interleaved order of
 // launch_pack_gate_up. tiled: u in tile order.
-template <typename T>
-hipError_t launch_swiglu(const float* part, int S, int M, int F, T* u, bool tiled,
-                         hipStream_t st);
+hipError_t launch_swiglu_bf16(const float* part, int S, int M, int F, uint16_t* u, bool tiled,
+                              hipStream_t st);
 
 // dst[m][k] (row-major, at most dst_elems elements) = src (tile order, [M][K]).
 hipError_t launch_untile(const uint16_t* src, int M, int K, uint16_t* dst, int64_t dst_elems,
                          hipStream_t st);
 
 // y = x1 + sum_s part[s];  out[row_idx ? row_idx[i] : i] = y.
-template <typename T>
-hipError_t launch_residual_scatter(const float* part, int S, int M, int d, const float* x1,
-                                   T* out, const int32_t* row_idx, hipStream_t st);
+hipError_t launch_residual_scatter_bf16(const float* part, int S, int M, int d, const float* x1,
+                                        uint16_t* out, const int32_t* row_idx, hipStream_t st);
 
 // Bit copy of [n][Hkv][hd] keys/values into the paged cache.
 template <typename T>

@@ -9,8 +9,6 @@
 // (row, column chunk) rather than one workgroup per row where no row-wide
 // reduction is needed. Every reduction order is fixed by the block shape and
 // S alone, so a row's result never depends on the other rows of the call.
-#include <type_traits>
-
 #include "common.h"
 #include "kernels.h"
 
@@ -60,11 +58,10 @@ __device__ __forceinline__ u32x4_t pack_bf16x8(const float* f) {
 }  // namespace
 
 // ----------------------------------------------------------------------------
-// Segment-boundary gather of the sub-batch rows, fused with the first RMSNorm.
-// ----------------------------------------------------------------------------
-// Prefill row slots: row_info[i] = (position clamped to the RoPE table,
+// Segment-boundary gather of the sub-batch rows, fused with the first RMSNorm,
+// and the prefill row slots: row_info[i] = (position clamped to the RoPE table,
 // cache block of the position), for the QKV projection's fused epilogue.
-// bf16 rows, d % 8 == 0: 16-byte vectors, row held in registers.
+// d % 8 == 0: 16-byte vectors, row held in registers.
 //   * Row of a workgroup: consecutive rows run on one XCD
 //     (blockIdx % 8 is the XCD), so the 16 rows that share each 1 KB
 //     tile-order block fill it in that XCD's L2 and it leaves as whole lines;
@@ -72,6 +69,7 @@ __device__ __forceinline__ u32x4_t pack_bf16x8(const float* f) {
 //     scalar loads through the constant address space, which wait on their
 //     own counter, so the chain of dependent loads overlaps the row's vector
 //     loads instead of following them.
+// ----------------------------------------------------------------------------
 typedef __attribute__((address_space(4))) const int32_t* cint_ptr;
 
 __device__ __forceinline__ void write_row_slot_uniform(const RowSlotArgs& rs, int i) {
@@ -199,17 +197,17 @@ hipError_t launch_rope_table(const double* inv_freq, int half, int n_pos, float*
 // once per workgroup into LDS), store queries, append the rotated key and the
 // value to the sequence's cache slot. The partial loads, which depend on
 // nothing, are issued first; the cache slot lookup and the angles overlap
-// them (a dependent load of the RoPE table measured slower here). In decode,
-// one wave also writes the decode attention's work list.
+// them (a dependent load of the RoPE table measured slower here). One wave
+// also writes the decode attention's work list.
 // ----------------------------------------------------------------------------
 constexpr int kEpiHeads = 8;
 
-template <typename T, int S>
+template <int S>
 __global__ __launch_bounds__(kEpiHeads * kWave) void qkv_epilogue_kernel(
     const float* __restrict__ part, int M, int Hq, int Hkv, int hd,
-    const int32_t* __restrict__ positions, const int32_t* __restrict__ seq_starts, int n_seqs,
-    const int32_t* __restrict__ block_table, int max_blocks, const double* __restrict__ inv_freq,
-    T* __restrict__ q_out, T* __restrict__ k_cache, T* __restrict__ v_cache,
+    const int32_t* __restrict__ positions, const int32_t* __restrict__ block_table,
+    int max_blocks, const double* __restrict__ inv_freq, bf16_t* __restrict__ q_out,
+    bf16_t* __restrict__ k_cache, bf16_t* __restrict__ v_cache,
     const int32_t* __restrict__ ctx_lens, int32_t* __restrict__ split_off, int max_splits,
     const float* __restrict__ ss, int d, float eps) {
   __shared__ float rot[2][128];  // cos, sin of the row's angles (hd / 2 <= 128)
@@ -245,17 +243,12 @@ __global__ __launch_bounds__(kEpiHeads * kWave) void qkv_epilogue_kernel(
   }
   // RMSNorm_1 folded into the projection: this row's 1/rms from the
   // per-slice sums of squares, added in slice order.
-  float rscale = 1.f;
-  if (ss != nullptr) {
-    const float t = sum_parts1<S>(ss + i, M);
-    rscale = 1.0f / sqrtf(t / (float)d + eps);
-  }
+  const float rscale = 1.0f / sqrtf(sum_parts1<S>(ss + i, M) / (float)d + eps);
   const int pos = positions[i];
   int64_t blk = 0;
   int slot = 0;
   if (live && h >= Hq) {
-    const int seq = row_to_seq(seq_starts, n_seqs, i);
-    blk = block_table[(int64_t)seq * max_blocks + pos / kBlockTokens];
+    blk = block_table[(int64_t)i * max_blocks + pos / kBlockTokens];
     slot = pos % kBlockTokens;
   }
   // The row's rotation angles in fp64, once for all the heads of the block.
@@ -266,22 +259,22 @@ __global__ __launch_bounds__(kEpiHeads * kWave) void qkv_epilogue_kernel(
     rot[1][j] = (float)sn;
   }
   __syncthreads();
-  if (split_off != nullptr && blockIdx.x == 0 && i == 0 && wv == 0) {
+  if (blockIdx.x == 0 && i == 0 && wv == 0) {
     // Decode attention work list over the n = min(ctx_lens[s], positions[s]
     // + 1) keys row s attends, in 256-key partitions (at most max_splits; only
     // invalid lengths reach the cap). First every full partition: an
-    // exclusive prefix sum of their counts in split_off[0 .. n_seqs]. Then
+    // exclusive prefix sum of their counts in split_off[0 .. M]. Then
     // each sequence's last partition if it is partial, largest first: their
-    // count in split_off[n_seqs + 1], the sequences in that order from
-    // split_off[n_seqs + 2]. Dealt out in that order (snake-wise over the
+    // count in split_off[M + 1], the sequences in that order from
+    // split_off[M + 2]. Dealt out in that order (snake-wise over the
     // workgroups), items of similar size meet at the end of the kernel.
     for (int r = lane; r < kDecodeSplit; r += kWave) wl_rank[r] = 0;
     wave_lds_order();  // wl_rank is counted, read and moved by this wave alone
     int run = 0;
     if (lane == 0) split_off[0] = 0;
-    for (int base = 0; base < n_seqs; base += kWave) {
+    for (int base = 0; base < M; base += kWave) {
       const int s = base + lane;
-      const int n = s < n_seqs ? max(0, min(ctx_lens[s], positions[s] + 1)) : 0;
+      const int n = s < M ? max(0, min(ctx_lens[s], positions[s] + 1)) : 0;
       const int nsp = (n + kDecodeSplit - 1) / kDecodeSplit;
       const int rem = (nsp <= max_splits) ? n % kDecodeSplit : 0;
       int v = min(nsp, max_splits) - (rem != 0);
@@ -291,7 +284,7 @@ __global__ __launch_bounds__(kEpiHeads * kWave) void qkv_epilogue_kernel(
         const int t = __shfl_up(v, o, kWave);
         if (lane >= o) v += t;
       }
-      if (s < n_seqs) split_off[s + 1] = run + v;
+      if (s < M) split_off[s + 1] = run + v;
       run += __shfl(v, kWave - 1, kWave);
     }
     wave_lds_order();
@@ -316,14 +309,14 @@ __global__ __launch_bounds__(kEpiHeads * kWave) void qkv_epilogue_kernel(
       wl_rank[kDecodeSplit - 1 - (lane * 4 + e)] = acc;
       acc += c[e];
     }
-    if (lane == kWave - 1) split_off[n_seqs + 1] = incl;
+    if (lane == kWave - 1) split_off[M + 1] = incl;
     wave_lds_order();
-    for (int base = 0; base < n_seqs; base += kWave) {
+    for (int base = 0; base < M; base += kWave) {
       const int s = base + lane;
-      const int n = s < n_seqs ? max(0, min(ctx_lens[s], positions[s] + 1)) : 0;
+      const int n = s < M ? max(0, min(ctx_lens[s], positions[s] + 1)) : 0;
       const int nsp = (n + kDecodeSplit - 1) / kDecodeSplit;
       const int rem = (nsp <= max_splits) ? n % kDecodeSplit : 0;
-      if (rem != 0) split_off[n_seqs + 2 + atomicAdd(&wl_rank[rem], 1)] = s;
+      if (rem != 0) split_off[M + 2 + atomicAdd(&wl_rank[rem], 1)] = s;
     }
   }
   if (!live) return;
@@ -338,52 +331,50 @@ __global__ __launch_bounds__(kEpiHeads * kWave) void qkv_epilogue_kernel(
         const float c = rot[0][j], sn = rot[1][j];
         const float rlo = lo * c - hi * sn, rhi = hi * c + lo * sn;
         if (h < Hq) {
-          T* dst = q_out + ((int64_t)i * Hq + h) * hd;
-          Elem<T>::store(dst + j, rlo);
-          Elem<T>::store(dst + j + half, rhi);
+          bf16_t* dst = q_out + ((int64_t)i * Hq + h) * hd;
+          dst[j] = (bf16_t)f32_to_bf16(rlo);
+          dst[j + half] = (bf16_t)f32_to_bf16(rhi);
         } else {
-          T* tile = k_cache + (blk * Hkv + (h - Hq)) * kBlockTokens * hd;
-          Elem<T>::store(tile + k_tile_offset(slot, j), rlo);
-          Elem<T>::store(tile + k_tile_offset(slot, j + half), rhi);
+          bf16_t* tile = k_cache + (blk * Hkv + (h - Hq)) * kBlockTokens * hd;
+          tile[k_tile_offset(slot, j)] = (bf16_t)f32_to_bf16(rlo);
+          tile[k_tile_offset(slot, j + half)] = (bf16_t)f32_to_bf16(rhi);
         }
       }
     }
   } else {
-    T* tile = v_cache + (blk * Hkv + (h - Hq - Hkv)) * kBlockTokens * hd;
+    bf16_t* tile = v_cache + (blk * Hkv + (h - Hq - Hkv)) * kBlockTokens * hd;
 #pragma unroll
     for (int t = 0; t < 4; ++t) {
       const int e = lane + kWave * t;
-      if (e < hd) Elem<T>::store(tile + v_tile_offset(slot, e), val[t]);
+      if (e < hd) tile[v_tile_offset(slot, e)] = (bf16_t)f32_to_bf16(val[t]);
     }
   }
 }
 
+// S is skinny_plan's: a power of two.
 #define COCO_SWITCH_S(S, ...)                        \
   switch (S) {                                       \
     case 1: { constexpr int S_ = 1; __VA_ARGS__; } break;  \
     case 2: { constexpr int S_ = 2; __VA_ARGS__; } break;  \
-    case 3: { constexpr int S_ = 3; __VA_ARGS__; } break;  \
     case 4: { constexpr int S_ = 4; __VA_ARGS__; } break;  \
     case 8: { constexpr int S_ = 8; __VA_ARGS__; } break;  \
     case 16: { constexpr int S_ = 16; __VA_ARGS__; } break; \
     default: return hipErrorInvalidValue;            \
   }
 
-template <typename T>
-hipError_t launch_qkv_epilogue(const float* part, int S, int M, int Hq, int Hkv, int hd,
-                               const int32_t* positions, const int32_t* seq_starts,
-                               int n_seqs, const int32_t* block_table, int max_blocks,
-                               const double* inv_freq, T* q_out, T* k_cache, T* v_cache,
-                               const int32_t* ctx_lens, int32_t* split_off, int max_splits,
-                               const float* ss, int d, float eps, hipStream_t st) {
+hipError_t launch_qkv_epilogue_bf16(const float* part, int S, int M, int Hq, int Hkv, int hd,
+                                    const int32_t* positions, const int32_t* block_table,
+                                    int max_blocks, const double* inv_freq, bf16_t* q_out,
+                                    bf16_t* k_cache, bf16_t* v_cache, const int32_t* ctx_lens,
+                                    int32_t* split_off, int max_splits, const float* ss, int d,
+                                    float eps, hipStream_t st) {
   if (M <= 0) return hipSuccess;
-  if (hd > 256 || hd % 2 != 0) return hipErrorInvalidValue;
+  if (hd > 256 || hd % 2 != 0 || !ss || !split_off) return hipErrorInvalidValue;
   const dim3 grid((Hq + 2 * Hkv + kEpiHeads - 1) / kEpiHeads, M);
-  COCO_SWITCH_S(S, COCO_LAUNCH((qkv_epilogue_kernel<T, S_>), grid,
-                                      dim3(kEpiHeads * kWave), 0, st,
-                                      part, M, Hq, Hkv, hd, positions, seq_starts, n_seqs,
-                                      block_table, max_blocks, inv_freq, q_out, k_cache,
-                                      v_cache, ctx_lens, split_off, max_splits, ss, d, eps));
+  COCO_SWITCH_S(S, COCO_LAUNCH((qkv_epilogue_kernel<S_>), grid, dim3(kEpiHeads * kWave), 0, st,
+                               part, M, Hq, Hkv, hd, positions, block_table, max_blocks,
+                               inv_freq, q_out, k_cache, v_cache, ctx_lens, split_off,
+                               max_splits, ss, d, eps));
   return hipGetLastError();
 }
 
@@ -391,22 +382,17 @@ hipError_t launch_qkv_epilogue(const float* part, int S, int M, int Hq, int Hkv,
 // O-projection epilogue: residual add (kept in fp32) fused with RMSNorm_2.
 // One 1024-thread workgroup per row; every thread owns 4-column vectors.
 // ----------------------------------------------------------------------------
-template <typename T>
-__device__ __forceinline__ f32x4_t load4(const T* p);
-template <>
-__device__ __forceinline__ f32x4_t load4<float>(const float* p) { return *(const f32x4_t*)p; }
-template <>
-__device__ __forceinline__ f32x4_t load4<bf16_t>(const bf16_t* p) {
+__device__ __forceinline__ f32x4_t load4(const bf16_t* p) {
   const u32x2_t u = *(const u32x2_t*)p;
   return f32x4_t{__uint_as_float(u.x << 16), __uint_as_float(u.x & 0xFFFF0000u),
                  __uint_as_float(u.y << 16), __uint_as_float(u.y & 0xFFFF0000u)};
 }
 
-template <typename T, int S>
+template <int S>
 __global__ __launch_bounds__(kNormThreads) void residual_rmsnorm_kernel(
-    const float* __restrict__ part, int M, int d, const T* __restrict__ x,
-    const int32_t* __restrict__ row_idx, const T* __restrict__ gamma, float eps,
-    float* __restrict__ x1, T* __restrict__ h2, bool tiled) {
+    const float* __restrict__ part, int M, int d, const bf16_t* __restrict__ x,
+    const int32_t* __restrict__ row_idx, const bf16_t* __restrict__ gamma, float eps,
+    float* __restrict__ x1, bf16_t* __restrict__ h2, bool tiled) {
   __shared__ float red[kNormThreads / kWave];
   constexpr int kMaxVec = 4;  // d <= 16384
   const int i = blockIdx.x;
@@ -421,8 +407,8 @@ __global__ __launch_bounds__(kNormThreads) void residual_rmsnorm_kernel(
     if (v < nv) {
       const int c = 4 * v;
       a[u] = sum_parts4<S>(part + (int64_t)i * d + c, pstride);
-      xr[u] = load4<T>(x + xr_row * d + c);
-      g[u] = load4<T>(gamma + c);
+      xr[u] = load4(x + xr_row * d + c);
+      g[u] = load4(gamma + c);
     }
   }
   float ss = 0.f;
@@ -446,23 +432,21 @@ __global__ __launch_bounds__(kNormThreads) void residual_rmsnorm_kernel(
     if (v < nv) {
       const int c = 4 * v;
       // Four columns from a multiple of 4 stay contiguous in tile order.
-      T* dst = h2 + (tiled ? tile_off(i, c, d) : (int64_t)i * d + c);
+      bf16_t* dst = h2 + (tiled ? tile_off(i, c, d) : (int64_t)i * d + c);
       store4(dst, a[u][0] * inv * g[u][0], a[u][1] * inv * g[u][1], a[u][2] * inv * g[u][2],
              a[u][3] * inv * g[u][3]);
     }
   }
 }
 
-template <typename T>
-hipError_t launch_residual_rmsnorm(const float* part, int S, int M, int d, const T* x,
-                                   const int32_t* row_idx, const T* gamma, float eps, float* x1,
-                                   T* h2, bool tiled, hipStream_t st) {
+hipError_t launch_residual_rmsnorm_bf16(const float* part, int S, int M, int d, const bf16_t* x,
+                                        const int32_t* row_idx, const bf16_t* gamma, float eps,
+                                        float* x1, bf16_t* h2, bool tiled, hipStream_t st) {
   if (M <= 0) return hipSuccess;
   if (d % 4 != 0 || d > 4 * 4 * kNormThreads) return hipErrorInvalidValue;
-  if (tiled && (!std::is_same<T, bf16_t>::value || d % 32 != 0)) return hipErrorInvalidValue;
-  COCO_SWITCH_S(S, COCO_LAUNCH((residual_rmsnorm_kernel<T, S_>), dim3(M),
-                                      dim3(kNormThreads), 0, st, part, M, d, x, row_idx, gamma,
-                                      eps, x1, h2, tiled));
+  if (tiled && d % 32 != 0) return hipErrorInvalidValue;
+  COCO_SWITCH_S(S, COCO_LAUNCH((residual_rmsnorm_kernel<S_>), dim3(M), dim3(kNormThreads), 0, st,
+                               part, M, d, x, row_idx, gamma, eps, x1, h2, tiled));
   return hipGetLastError();
 }
 
@@ -470,9 +454,9 @@ hipError_t launch_residual_rmsnorm(const float* part, int S, int M, int d, const
 // SwiGLU: u = silu(gate) * up from the reduced gate/up partials; 4 columns
 // per thread.
 // ----------------------------------------------------------------------------
-template <typename T, int S>
+template <int S>
 __global__ __launch_bounds__(kRowThreads) void swiglu_kernel(const float* __restrict__ part,
-                                                             int M, int F, T* __restrict__ u,
+                                                             int M, int F, bf16_t* __restrict__ u,
                                                              bool tiled) {
   const int i = blockIdx.y;
   const int c = 4 * (blockIdx.x * kRowThreads + threadIdx.x);
@@ -482,22 +466,21 @@ __global__ __launch_bounds__(kRowThreads) void swiglu_kernel(const float* __rest
   const float* p = part + (int64_t)i * 2 * F + 2 * c - (c & 7);
   const f32x4_t g = sum_parts4<S>(p, pstride);
   const f32x4_t up = sum_parts4<S>(p + 8, pstride);
-  T* dst = u + (tiled ? tile_off(i, c, F) : (int64_t)i * F + c);
+  bf16_t* dst = u + (tiled ? tile_off(i, c, F) : (int64_t)i * F + c);
   float r[4];
 #pragma unroll
   for (int e = 0; e < 4; ++e) r[e] = silu_mul(g[e], up[e]);
   store4(dst, r[0], r[1], r[2], r[3]);
 }
 
-template <typename T>
-hipError_t launch_swiglu(const float* part, int S, int M, int F, T* u, bool tiled,
-                         hipStream_t st) {
+hipError_t launch_swiglu_bf16(const float* part, int S, int M, int F, bf16_t* u, bool tiled,
+                              hipStream_t st) {
   if (M <= 0) return hipSuccess;
   if (F % 4 != 0) return hipErrorInvalidValue;
-  if (tiled && (!std::is_same<T, bf16_t>::value || F % 32 != 0)) return hipErrorInvalidValue;
+  if (tiled && F % 32 != 0) return hipErrorInvalidValue;
   const dim3 grid((F / 4 + kRowThreads - 1) / kRowThreads, M);
-  COCO_SWITCH_S(S, COCO_LAUNCH((swiglu_kernel<T, S_>), grid, dim3(kRowThreads), 0, st,
-                                      part, M, F, u, tiled));
+  COCO_SWITCH_S(S, COCO_LAUNCH((swiglu_kernel<S_>), grid, dim3(kRowThreads), 0, st, part, M, F,
+                               u, tiled));
   return hipGetLastError();
 }
 
@@ -533,10 +516,10 @@ hipError_t launch_untile(const uint16_t* src, int M, int K, uint16_t* dst, int64
 // Down-projection epilogue: y = x1 + sum of partials, rounded to the hidden
 // dtype, scattered to the row's place in the full-batch buffer.
 // ----------------------------------------------------------------------------
-template <typename T, int S>
+template <int S>
 __global__ __launch_bounds__(kRowThreads) void residual_scatter_kernel(
     const float* __restrict__ part, int M, int d, const float* __restrict__ x1,
-    T* __restrict__ out, const int32_t* __restrict__ row_idx) {
+    bf16_t* __restrict__ out, const int32_t* __restrict__ row_idx) {
   const int i = blockIdx.y;
   const int c = 4 * (blockIdx.x * kRowThreads + threadIdx.x);
   if (c >= d) return;
@@ -544,17 +527,16 @@ __global__ __launch_bounds__(kRowThreads) void residual_scatter_kernel(
   const f32x4_t a = sum_parts4<S>(part + (int64_t)i * d + c, (int64_t)M * d);
   const f32x4_t x = *(const f32x4_t*)(x1 + (int64_t)i * d + c);
 #pragma unroll
-  for (int e = 0; e < 4; ++e) Elem<T>::store(out + r * d + c + e, x[e] + a[e]);
+  for (int e = 0; e < 4; ++e) out[r * d + c + e] = (bf16_t)f32_to_bf16(x[e] + a[e]);
 }
 
-template <typename T>
-hipError_t launch_residual_scatter(const float* part, int S, int M, int d, const float* x1,
-                                   T* out, const int32_t* row_idx, hipStream_t st) {
+hipError_t launch_residual_scatter_bf16(const float* part, int S, int M, int d, const float* x1,
+                                        bf16_t* out, const int32_t* row_idx, hipStream_t st) {
   if (M <= 0) return hipSuccess;
   if (d % 4 != 0) return hipErrorInvalidValue;
   const dim3 grid((d / 4 + kRowThreads - 1) / kRowThreads, M);
-  COCO_SWITCH_S(S, COCO_LAUNCH((residual_scatter_kernel<T, S_>), grid, dim3(kRowThreads),
-                                      0, st, part, M, d, x1, out, row_idx));
+  COCO_SWITCH_S(S, COCO_LAUNCH((residual_scatter_kernel<S_>), grid, dim3(kRowThreads), 0, st,
+                               part, M, d, x1, out, row_idx));
   return hipGetLastError();
 }
 
@@ -720,18 +702,6 @@ hipError_t launch_kv_append(const T* k, const T* v, const int32_t* seq_idx,
   return hipGetLastError();
 }
 
-template hipError_t launch_qkv_epilogue<bf16_t>(const float*, int, int, int, int, int,
-                                                const int32_t*, const int32_t*, int,
-                                                const int32_t*, int, const double*, bf16_t*,
-                                                bf16_t*, bf16_t*, const int32_t*, int32_t*, int,
-                                                const float*, int, float, hipStream_t);
-template hipError_t launch_residual_rmsnorm<bf16_t>(const float*, int, int, int, const bf16_t*,
-                                                    const int32_t*, const bf16_t*, float, float*,
-                                                    bf16_t*, bool, hipStream_t);
-template hipError_t launch_swiglu<bf16_t>(const float*, int, int, int, bf16_t*, bool,
-                                          hipStream_t);
-template hipError_t launch_residual_scatter<bf16_t>(const float*, int, int, int, const float*,
-                                                    bf16_t*, const int32_t*, hipStream_t);
 template hipError_t launch_kv_append<bf16_t>(const bf16_t*, const bf16_t*, const int32_t*,
                                              const int32_t*, int, int, int, const int32_t*, int,
                                              bf16_t*, bf16_t*, hipStream_t);
