@@ -133,11 +133,11 @@ size_t align256(size_t b) { return (b + 255) & ~(size_t)255; }
 
 int elem_bytes(int dtype) { return dtype == COCO_BF16 ? 2 : 4; }
 
-// Fp32 partials [splits][rows][N] that `part` has room for: the decode GEMMs'
-// K-slices, and at least one per 8192 k (up to four) where N < 12,288. The
-// prefill GEMMs write none; the floor keeps the size of a call's buffers, and
-// with it which calls the no-alloc entry point takes, what it was when
-// they split long K.
+// Fp32 partials [splits][rows][N] that `part` counts: the decode GEMMs'
+// K-slices, and at least one per 8192 k (up to four) where N <= 12,032. The
+// prefill and fp32 GEMMs write none; the floor and fp32's one split keep the
+// size of a call's buffers, and with it which calls the no-alloc entry point
+// takes.
 int part_splits(const coco_layer_config& c, int N, int K) {
   if (c.dtype != COCO_BF16) return 1;
   int S = 1;
@@ -152,9 +152,10 @@ int part_splits(const coco_layer_config& c, int N, int K) {
 
 // Lays out the per-call buffers for `rows` call rows and `dec_seqs` decode
 // sequences from `base`, each piece 256-byte aligned, and returns the bytes
-// they take (base == nullptr: sizes only; `w` may then be null).
+// they take (base == nullptr: sizes only; `w` may then be null). *used: the
+// bytes that must be there; an fp32 layer touches nothing past x1.
 size_t carve_work(const coco_layer_config& c, int64_t rows, int64_t dec_seqs, int max_splits,
-                  char* base, Work* w) {
+                  char* base, Work* w, size_t* used = nullptr) {
   const int eb = elem_bytes(c.dtype);
   const int64_t R = rows, d = c.d_model, F = c.d_ffn;
   const int64_t qd = (int64_t)c.n_q_heads * c.head_dim;
@@ -189,6 +190,7 @@ size_t carve_work(const coco_layer_config& c, int64_t rows, int64_t dec_seqs, in
     off[i] = total;
     total += sizes[i];
   }
+  if (used) *used = bf ? total : off[7];
   if (base && w) {
     w->x = base + off[0];
     w->h = base + off[1];
@@ -197,6 +199,7 @@ size_t carve_work(const coco_layer_config& c, int64_t rows, int64_t dec_seqs, in
     w->h2 = base + off[4];
     w->u = base + off[5];
     w->x1 = (float*)(base + off[6]);
+    if (!bf) return total;
     w->part = (float*)(base + off[7]);
     w->attn_o = (float*)(base + off[8]);
     w->attn_ml = (float*)(base + off[9]);
@@ -391,7 +394,8 @@ int coco_layer_init(const coco_layer_config* cfg, const coco_layer_weights* laye
   // inverse frequencies and (bf16) the RoPE table of the fused prefill QKV
   // epilogue.
   H->rope_rows = c.dtype == COCO_BF16 ? c.max_blocks_per_seq * kBlockTokens : 0;
-  const size_t work_bytes = carve_work(c, R, H->dec_rows, H->max_splits, nullptr, nullptr);
+  size_t work_bytes = 0;
+  carve_work(c, R, H->dec_rows, H->max_splits, nullptr, nullptr, &work_bytes);
   const size_t freq_bytes = align256((size_t)(c.head_dim / 2) * 8);
   const size_t rope_bytes = align256((size_t)H->rope_rows * (c.head_dim / 2) * 8);
   H->ws_bytes = work_bytes + freq_bytes + rope_bytes;
