@@ -252,7 +252,8 @@ int coco_layer_workspace(coco_layer_t h, int32_t which, void* dst, int64_t dst_b
                          coco_stream_t stream);
 
 /* Per-kernel timing for benchmarks (calls of any handle are unaffected while
- * it is off; kinds whose work runs inside another kernel count no launches). When on, every kernel launched by coco_layer_forward /
+ * it is off; kinds whose work runs inside another kernel count no launches).
+ * When on, every kernel launched by coco_layer_forward /
  * coco_layer_span_forward on this handle is launched with a pair of HIP events
  * (hipExtLaunchKernelGGL) that the runtime timestamps at the kernel's own
  * start and end, from a pool of events created here (so switching it on

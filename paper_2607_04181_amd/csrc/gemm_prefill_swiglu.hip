@@ -14,7 +14,7 @@ namespace prefill {
 //     loads-only ablation of the 256-row tiles runs at 54-60);
 //   * its MFMAs, n TM TN / 64 cycles at an effective 1.47 GHz (the clock under
 //     load times the MFMA pipe's share of a stage).
-// The five constants are a least-squares fit to 2,100 timed launches (the 13
+// The four constants are a least-squares fit to 2,100 timed launches (the 13
 // shapes other than 192 x 256 and 160 x 256, x 15 row counts from 1 to 2,048 x
 // the four projections of the 8B, 32B and 70B layers): 13% rms off the times,
 // and the shape it picks takes on average 0.1%, at worst 6% longer than the

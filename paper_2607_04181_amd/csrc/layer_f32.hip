@@ -20,7 +20,7 @@
 // neighbouring lanes hold different rows, a load touches 16 lines and takes
 // ~75 cycles (gate/up of 200 rows, d = 1024: 60 against 39 us). Against 16 x 16 LDS
 // tiles, one output per thread, and ten launches: tiny layer (d = 256, 4
-// rows) 103 -> 28 us, d = 1024, 200-row prefill 588 -> 113 us.
+// rows) 103 -> 28 us, d = 1024, 200-row prefill 588 -> 109 us.
 // The order of every sum depends on K (or d) alone, not on M, RT or the other
 // rows.
 #include <type_traits>
