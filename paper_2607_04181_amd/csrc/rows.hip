@@ -550,7 +550,7 @@ hipError_t launch_residual_scatter_bf16(const float* part, int S, int M, int d, 
 // run's first token stores for all four, also those of the next workgroup's
 // tokens), other tokens element by element. One 2-byte store per element ran
 // at 1.9 TB/s (6000 tokens of 8 heads x 128, 49 MB read and written: 26.5 us);
-// 14.4 now, of which a loop of calls needs 13.3 on the host alone. (Runs found per workgroup
+// 14.5 now, of which a loop of calls needs 13.1 on the host alone. (Runs found per workgroup
 // by one ballot: with every wave looking them up token by token in LDS, it
 // stayed at 27 whatever the stores.)
 // ----------------------------------------------------------------------------
